@@ -52,7 +52,7 @@ struct Workspace {
   double* vmass = nullptr;    // [max units][max_batch] residual / bonus mass per unit
   double* vpart = nullptr;    // [max_batch][B+1][vchunks][2] target row (max, sum) per chunk
   // truncated sampling (top-k / top-p)
-  float* lf = nullptr;        // [Mmax][V]     logits of the current pass, row-major
+  float* lf = nullptr;        // [Mmax][V]     logits of the current pass of rows that truncate
   FState* fst = nullptr;      // [Mmax]        truncation state of each draft row (last pass)
   FState* tst = nullptr;      // [max_batch][B+1] truncation state of each target row
   uint8_t* filt = nullptr;    // [max_batch]   the row samples with truncation
@@ -146,10 +146,9 @@ hipError_t launch_lmhead_gemm(xp_handle* h, int M, const void* hidden, const uin
 hipError_t launch_pass(xp_handle* h, int batch, int pass, uint32_t flags, const int32_t* seed_ids,
                        const int32_t* anchor, int32_t* out_traj, hipStream_t st);
 int prep_ksp(int H);
-hipError_t launch_read(xp_handle* h, int batch, int pass, uint32_t flags, const uint8_t* temp,
-                       float* out_logits, hipStream_t st);
-hipError_t launch_finish(xp_handle* h, int batch, int K, uint32_t flags, int32_t* out_ids,
-                         int32_t* out_iters, float* out_logits, hipStream_t st, bool filtering);
+hipError_t launch_read(xp_handle* h, int batch, uint32_t flags, const uint8_t* temp, bool lf,
+                       float* out, hipStream_t st);
+hipError_t launch_base_logits(xp_handle* h, int batch, float* out_logits, hipStream_t st);
 hipError_t launch_verify(xp_handle* h, int batch, const int32_t* draft_ids, const uint8_t* temp,
                          const int32_t* target_ids, const float* target_logits,
                          const float* r_accept, const float* u_res, int32_t* out_n,

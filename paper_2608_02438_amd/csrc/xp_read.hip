@@ -10,6 +10,33 @@
 
 namespace xp {
 
+// Where a Read writes logit rows ([M][V] fp32, row-major): every position's to
+// `out` (the caller's logits, written by the last pass only), those of rows
+// that truncate (filt) to `lf` (the workspace rows their sampler reads, every
+// pass).  Either may be null.  vec: V is a multiple of 4 and both are 16-byte
+// aligned, so a lane's four consecutive rows go out as one 16-byte store and a
+// tile's 16 rows of a position fill a 64-byte segment with one instruction.
+// Six passes with the logits at V = 151936, against every pass storing them 4
+// bytes at a time: a refine + verify step of 2048 positions 8.33 -> 5.10 ms,
+// of 512 positions 2.17 -> 1.36 ms, of 128 positions 0.94 -> 0.74 ms.
+struct LogitRows {
+  float* out;
+  float* lf;
+  const uint8_t* filt;
+  int vec;
+};
+
+__device__ __forceinline__ void put_rows(float* dst, size_t at, const floatx4& v, int row0, int V,
+                                         bool vec) {
+  if (vec) {
+    if (row0 < V) *reinterpret_cast<floatx4*>(dst + at) = v;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (row0 + i < V) dst[at + i] = v[i];
+  }
+}
+
 // ---------------------------------------------------------------------------
 // A7: l = s + W_r z, r = 256.  Every wave streams its own unit of tiles with
 // the full k range (one chain of MFMAs per tile, seeded with s); the position
@@ -24,8 +51,8 @@ template <typename T>
 __global__ __launch_bounds__(kReadWaves * kWave) void k_read(
     const T* __restrict__ W, const T* __restrict__ Z, const float* __restrict__ S, int Ms, int V,
     int M, int ntiles, int U, uint64_t* __restrict__ keys, Stat* __restrict__ stats,
-    const uint8_t* __restrict__ temp, int B, float* __restrict__ out_logits,
-    const int32_t* __restrict__ ctrl, int skip_when_done, const float* __restrict__ invT) {
+    const uint8_t* __restrict__ temp, int B, LogitRows rows, const int32_t* __restrict__ ctrl,
+    int skip_when_done, const float* __restrict__ invT) {
   if (skip_when_done && ctrl[1]) return;          // every sequence is at its fixed point
   constexpr int NU = ReadTile<T>::NU;
   constexpr int NR = sizeof(T) == 2 ? 5 : 2;      // resident tiles per wave (32 / 64 VGPRs each)
@@ -43,6 +70,8 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read(
   const bool act = p < M;
   const int pc = act ? p : M - 1;
   const float pit = invT[pc / B];               // sampled rows: softmax(l / T)
+  const bool to_lf = rows.lf != nullptr && act && rows.filt[pc / B] != 0;
+  const bool to_out = rows.out != nullptr && act;
   uint64_t best = kKeyMin;
   Stat st = stat_empty();
   bool sample = false;
@@ -67,11 +96,8 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read(
         st.s = v ? nx.s : st.s;
       }
     }
-    if (out_logits) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (act && row0 + i < V) out_logits[(size_t)p * V + row0 + i] = acc[i];
-    }
+    if (to_out) put_rows(rows.out, (size_t)p * V + row0, acc, row0, V, rows.vec);
+    if (to_lf) put_rows(rows.lf, (size_t)p * V + row0, acc, row0, V, rows.vec);
   };
   // z fragments, read once from LDS into registers after the barrier
   u32x4 zr[NU];
@@ -241,6 +267,8 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read(
 constexpr int kRmLds = 163840;                   // bytes of LDS the ring may take
 constexpr int kRmMaxStages = 8;
 constexpr int kRmMaxP = 4;                       // position blocks per wave (launch cap)
+constexpr int kRmOutLd = 36;                     // floats per position of a store buffer (32 + pad)
+constexpr int kRmOutWave = 16 * kRmOutLd;        // floats of a wave's store buffer
 
 // W_r tile in LDS: 16 rows x 32 chunks of 16 bytes, chunk c of row r at slot
 // 32 r + (c ^ r); s of 16 positions x 16 rows: chunk c (4 rows) of position q
@@ -254,12 +282,22 @@ __device__ __forceinline__ int rm_sslot(int q, int c) { return 4 * q + ((c ^ (q 
 // issues the same number of loads per tile, which the waits count on, and its
 // part of each W_r tile, which the other waves read), and its products,
 // selection partials and outputs are skipped.
-template <int P, bool EE>
+//
+// WM: how logit rows are written (LogitRows).  0: not at all.  1: straight from
+// the accumulators, 16 bytes per lane (rows.vec).  2: V or a pointer is not
+// 16-byte aligned; two tiles' values of 16 positions pass through a per-wave
+// LDS buffer, so that a store instruction writes 32 consecutive rows of two
+// positions instead of 4 bytes in each of 64 places; the buffer takes 18 KB
+// from the ring.  (V = 151935, H = 1024: the step at 2048 positions 8.52 ->
+// 3.63 ms, at 512 positions 2.22 -> 0.97 ms, at 128 positions 0.71 -> 0.55 ms.)
+// A wait count that leaves the stores of the later tiles outstanding too gained
+// nothing (5.10 against 5.11 ms at 2048 positions).
+template <int P, bool EE, int WM>
 __global__ __launch_bounds__(kReadWaves * kWave) void k_read_multi(
     const uint16_t* __restrict__ W, const uint16_t* __restrict__ Z, const float* __restrict__ S,
     int Ms, int V, int M, int ntiles, int U, uint64_t* __restrict__ keys,
     Stat* __restrict__ stats, const uint8_t* __restrict__ temp, int B,
-    float* __restrict__ out_logits, const int32_t* __restrict__ ctrl, int skip_when_done,
+    LogitRows rows, const int32_t* __restrict__ ctrl, int skip_when_done,
     int nwg, int ny, int gs, const float* __restrict__ invT, const int32_t* __restrict__ iters) {
   static_assert(kReadWaves == 8, "one 1 KB load per wave fills a 16-row tile");
   if (skip_when_done && ctrl[1]) return;          // every sequence is at its fixed point
@@ -282,9 +320,10 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read_multi(
   const int t0 = unit_tile_lo(u_lo, ntiles, U), n = unit_tile_lo(u_hi, ntiles, U) - t0;
   const int pw = py * (kReadWaves * kTile * P) + wave * (kTile * P);
   // as many stages as fit: the deeper the ring, the more tiles are in flight
-  constexpr int NS0 = kRmLds / ((WSL + SSL) * 16);
+  constexpr int kOut = WM == 2 ? kReadWaves * kRmOutWave : 0;   // floats of the store buffers
+  constexpr int NS0 = (kRmLds - 4 * kOut) / ((WSL + SSL) * 16);
   constexpr int kRmStages = NS0 < kRmMaxStages ? NS0 : kRmMaxStages;
-  __shared__ u32x4 lds[kRmStages * (WSL + SSL)];                // [stage][W tile | s]
+  __shared__ u32x4 lds[kRmStages * (WSL + SSL) + kOut / 4];     // [stage][W tile | s], buffers
   if (EE) {
     // early exit: nothing to do when every sequence of the workgroup's
     // positions is at its fixed point (the flag lives in the first ring
@@ -307,7 +346,7 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read_multi(
   u32x4 zf[P][NU];
 #pragma unroll
   for (int pb = 0; pb < P; ++pb) RT::load_z(Z, M, pw + kTile * pb, lane, zf[pb]);
-  bool act[P], sample[P];
+  bool act[P], sample[P], to_lf[P];
   float pit[P];                                   // sampled rows: softmax(l / T)
   bool any = false, live = false;
 #pragma unroll
@@ -317,6 +356,7 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read_multi(
     if (EE) live = live || (act[pb] && iters[(act[pb] ? p : M - 1) / B] == 0);
     sample[pb] = act[pb] && load_flag(temp, (act[pb] ? p : M - 1) / B, S) != 0;
     pit[pb] = invT[(act[pb] ? p : M - 1) / B];
+    to_lf[pb] = WM != 0 && rows.lf != nullptr && act[pb] && rows.filt[(act[pb] ? p : 0) / B] != 0;
     any = any || sample[pb];
   }
   const bool any_sample = __ballot(any) != 0;    // wave-uniform
@@ -409,6 +449,39 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read_multi(
     }
   };
 
+  // WM 2: the 32 rows from row lo of the wave's positions, from the even
+  // tile's values (lo, in c0) and the odd one's (c1); rows past hi - 1 are
+  // not written
+  float* obuf = reinterpret_cast<float*>(lds + kRmStages * (WSL + SSL)) + wave * kRmOutWave;
+  auto put_pair = [&](const floatx4 (&c0)[P], const floatx4 (&c1)[P], int lo, int hi) {
+    if constexpr (WM == 2) {
+      const int q = lane & 15, r4 = 4 * (lane >> 4), half = lane >> 5, r = lane & 31;
+      const uint32_t lane_at = (uint32_t)(half * V + r);
+#pragma unroll
+      for (int pb = 0; pb < P; ++pb) {
+        const uint32_t lfm = (uint32_t)__ballot(lane < 16 && to_lf[pb]);
+        *reinterpret_cast<floatx4*>(obuf + kRmOutLd * q + r4) = c0[pb];
+        *reinterpret_cast<floatx4*>(obuf + kRmOutLd * q + 16 + r4) = c1[pb];
+        wave_lds_order();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          // a wave-uniform address and one lane offset
+          const int pi = pw + kTile * pb + 2 * i, qp = 2 * i + half;
+          const size_t base = (size_t)pi * V + lo;
+          const float v = obuf[kRmOutLd * qp + r];
+          if (pi + half < M && lo + r < hi) {
+            if (rows.out) (rows.out + base)[lane_at] = v;
+            if ((lfm >> qp) & 1u) (rows.lf + base)[lane_at] = v;
+          }
+        }
+        wave_lds_order();
+      }
+    }
+  };
+  floatx4 held[P];                                // WM 2: the even tile of a pair
+#pragma unroll
+  for (int pb = 0; pb < P; ++pb) held[pb] = floatx4{0.f, 0.f, 0.f, 0.f};
+
   flush_until(t0);                                // units without tiles
   flush_keys(t0);                                 // read workgroups without tiles
 #pragma unroll
@@ -469,11 +542,21 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read_multi(
         for (int i = 0; i < 4; ++i) x[i] = sample[pb] ? acc[i] * pit[pb] : -INFINITY;
         st[pb] = stat_add4(st[pb], x[0], x[1], x[2], x[3]);
       }
-      if (out_logits) {
-        const int p = pw + kTile * pb + (lane & 15);
+      if (WM == 1) {
+        const size_t at = (size_t)(pw + kTile * pb + (lane & 15)) * V + row0;
+        if (rows.out && act[pb]) put_rows(rows.out, at, acc, row0, V, true);
+        if (to_lf[pb]) put_rows(rows.lf, at, acc, row0, V, true);
+      }
+    }
+    if (WM == 2) {
+      // pairs count from the workgroup's first tile; an odd last tile goes alone
+      if (j & 1) {
+        put_pair(held, accs, (t - 1) * kTile, min(V, (t + 1) * kTile));
+      } else if (j == n - 1) {
+        put_pair(accs, accs, t * kTile, min(V, (t + 1) * kTile));
+      } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (act[pb] && row0 + i < V) out_logits[(size_t)p * V + row0 + i] = acc[i];
+        for (int pb = 0; pb < P; ++pb) held[pb] = accs[pb];
       }
     }
     flush_until(t + 1);
@@ -482,12 +565,15 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read_multi(
   __builtin_amdgcn_s_waitcnt(0x0070);             // the clamped loads past the end
 }
 
-hipError_t launch_read(xp_handle* h, int batch, int pass, uint32_t flags, const uint8_t* temp,
-                       float* out_logits, hipStream_t st) {
-  (void)pass;
+// lf: the rows that truncate write their logits to the workspace; out: every
+// row writes them there too (either may be off).
+hipError_t launch_read(xp_handle* h, int batch, uint32_t flags, const uint8_t* temp, bool lf,
+                       float* out, hipStream_t st) {
   const int M = batch * h->B;
   dim3 grid(h->read_wgs, (M + kTile - 1) / kTile), block(kReadWaves * kWave);
   const int skip = (flags & XP_EARLY_EXIT) ? 1 : 0;
+  const LogitRows rows{out, lf ? h->ws.lf : nullptr, h->ws.filt,
+                       h->V % 4 == 0 && (uintptr_t)out % 16 == 0};
   if (h->dtype == XP_BF16 && M > kTile) {
     // 16 P positions per wave, P = 1..4 (P = 4 from 512 positions on)
     const int per = kReadWaves * kTile;
@@ -499,39 +585,45 @@ hipError_t launch_read(xp_handle* h, int batch, int pass, uint32_t flags, const 
     const int gs = ny;
     const int nsg = (h->read_wgs + gs - 1) / gs;
     grid = dim3((nsg + 7) / 8 * 8 * ny);
+    const int wm = out == nullptr && !lf ? 0 : (rows.vec ? 1 : 2);
     const uint16_t* Wr = (const uint16_t*)h->W_r;
     const uint16_t* Zb = (const uint16_t*)h->ws.z;
-#define XP_RM(PP, EEV)                                                                       \
-  hipLaunchKernelGGL((k_read_multi<PP, EEV>), grid, block, 0, st, Wr, Zb, h->ws.s, M, h->V, M, \
-                     h->ntiles, h->read_units, h->ws.keys, h->ws.stats, temp, h->B, out_logits, \
-                     h->ws.ctrl, skip, h->read_wgs, ny, gs, h->ws.invT, h->ws.iters)
+#define XP_RM(PP, EEV, WMV)                                                                  \
+  hipLaunchKernelGGL((k_read_multi<PP, EEV, WMV>), grid, block, 0, st, Wr, Zb, h->ws.s, M,     \
+                     h->V, M, h->ntiles, h->read_units, h->ws.keys, h->ws.stats, temp, h->B,   \
+                     rows, h->ws.ctrl, skip, h->read_wgs, ny, gs, h->ws.invT, h->ws.iters)
+#define XP_RM_W(PP, EEV)                                                                     \
+  do {                                                                                       \
+    if (wm == 0) XP_RM(PP, EEV, 0);                                                          \
+    else if (wm == 1) XP_RM(PP, EEV, 1);                                                     \
+    else XP_RM(PP, EEV, 2);                                                                  \
+  } while (0)
+#define XP_RM_P(EEV)                                                                         \
+  switch (P) {                                                                               \
+    case 1: XP_RM_W(1, EEV); break;                                                          \
+    case 2: XP_RM_W(2, EEV); break;                                                          \
+    case 3: XP_RM_W(3, EEV); break;                                                          \
+    default: XP_RM_W(4, EEV);                                                                \
+  }
     if (skip) {
-      switch (P) {
-        case 1: XP_RM(1, true); break;
-        case 2: XP_RM(2, true); break;
-        case 3: XP_RM(3, true); break;
-        default: XP_RM(4, true);
-      }
+      XP_RM_P(true)
     } else {
-      switch (P) {
-        case 1: XP_RM(1, false); break;
-        case 2: XP_RM(2, false); break;
-        case 3: XP_RM(3, false); break;
-        default: XP_RM(4, false);
-      }
+      XP_RM_P(false)
     }
+#undef XP_RM_P
+#undef XP_RM_W
 #undef XP_RM
     return hipGetLastError();
   }
   if (h->dtype == XP_BF16)
     hipLaunchKernelGGL((k_read<uint16_t>), grid, block, 0, st, (const uint16_t*)h->W_r,
                        (const uint16_t*)h->ws.z, h->ws.s, M, h->V, M, h->ntiles,
-                       h->read_units, h->ws.keys, h->ws.stats, temp, h->B, out_logits, h->ws.ctrl,
+                       h->read_units, h->ws.keys, h->ws.stats, temp, h->B, rows, h->ws.ctrl,
                        skip, h->ws.invT);
   else
     hipLaunchKernelGGL((k_read<float>), grid, block, 0, st, (const float*)h->W_r,
                        (const float*)h->ws.z, h->ws.s, M, h->V, M, h->ntiles, h->read_units,
-                       h->ws.keys, h->ws.stats, temp, h->B, out_logits, h->ws.ctrl, skip,
+                       h->ws.keys, h->ws.stats, temp, h->B, rows, h->ws.ctrl, skip,
                        h->ws.invT);
   return hipGetLastError();
 }

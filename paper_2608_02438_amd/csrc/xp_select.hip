@@ -288,14 +288,22 @@ __global__ __launch_bounds__(kSelWaves * kWave) void k_select(
   }
 }
 
-__global__ void k_copy_logits(int M, int V, const float* __restrict__ S,
-                              float* __restrict__ out) {
-  const size_t n = (size_t)M * V;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (size_t)gridDim.x * blockDim.x) {
-    const size_t p = i / V, v = i % V;
-    out[i] = S[s_index((int)p, (int)v, M)];
-  }
+// The base logits as rows (K = 0): [tile][position][16] to [position][V].  A
+// wave moves 64 rows (four tiles) of kCpPos positions; a load instruction reads
+// four 64-byte segments, and the neighbouring position's follow them in the
+// same lines; a store writes 256 consecutive bytes of a row.
+constexpr int kCpPos = 16;
+__global__ __launch_bounds__(256) void k_base_rows(int M, int V, const float* __restrict__ S,
+                                                   float* __restrict__ out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int row = (blockIdx.x * 4 + wave) * 64 + lane, p0 = blockIdx.y * kCpPos;
+  if (row >= V) return;
+  float v[kCpPos];
+#pragma unroll
+  for (int i = 0; i < kCpPos; ++i) v[i] = S[s_index(p0 + i < M ? p0 + i : M - 1, row, M)];
+#pragma unroll
+  for (int i = 0; i < kCpPos; ++i)
+    if (p0 + i < M) out[(size_t)(p0 + i) * V + row] = v[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -364,19 +372,10 @@ hipError_t launch_select(xp_handle* h, int batch, int pass, int K, uint32_t flag
   return hipGetLastError();
 }
 
-hipError_t launch_finish(xp_handle* h, int batch, int K, uint32_t flags, int32_t* out_ids,
-                         int32_t* out_iters, float* out_logits, hipStream_t st, bool filtering) {
-  (void)out_ids;
-  (void)out_iters;
+hipError_t launch_base_logits(xp_handle* h, int batch, float* out_logits, hipStream_t st) {
   const int M = batch * h->B;
-  if (K == 0 && (flags & XP_WRITE_LOGITS) && out_logits)
-    hipLaunchKernelGGL(k_copy_logits, dim3(1024), dim3(256), 0, st, M, h->V, h->ws.s,
-                       out_logits);
-  // with truncation every pass writes its logits to the workspace row buffer
-  // (the last executed pass's stay there): copy them out
-  if (K > 0 && filtering && (flags & XP_WRITE_LOGITS) && out_logits)
-    return hipMemcpyAsync(out_logits, h->ws.lf, (size_t)M * h->V * sizeof(float),
-                          hipMemcpyDeviceToDevice, st);
+  hipLaunchKernelGGL(k_base_rows, dim3((h->V + 255) / 256, (M + kCpPos - 1) / kCpPos), dim3(256),
+                     0, st, M, h->V, h->ws.s, out_logits);
   return hipGetLastError();
 }
 
