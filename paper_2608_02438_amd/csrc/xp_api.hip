@@ -164,6 +164,7 @@ extern "C" xp_status xp_create(const xp_weights* w, int32_t max_batch, xp_handle
       {(void**)&ws.lf, Mmax * w->V * 4},
       {(void**)&ws.fst, Mmax * sizeof(FState)},
       {(void**)&ws.tst, (size_t)max_batch * (w->B + 1) * sizeof(FState)},
+      {(void**)&ws.tumax, (size_t)max_batch * (w->B + 1) * target_units(w->V) * 4},
       {(void**)&ws.filt, (size_t)max_batch},
       {(void**)&ws.temp_nf, (size_t)max_batch},
       {(void**)&ws.fk, (size_t)max_batch * 4},

@@ -55,6 +55,7 @@ struct Workspace {
   float* lf = nullptr;        // [Mmax][V]     logits of the current pass of rows that truncate
   FState* fst = nullptr;      // [Mmax]        truncation state of each draft row (last pass)
   FState* tst = nullptr;      // [max_batch][B+1] truncation state of each target row
+  float* tumax = nullptr;     // [max_batch][B+1][target_units] unit maxima of the target rows
   uint8_t* filt = nullptr;    // [max_batch]   the row samples with truncation
   uint8_t* temp_nf = nullptr; // [max_batch]   the row samples without truncation
   int32_t* fk = nullptr;      // [max_batch]   effective top-k (0: none)
@@ -114,6 +115,7 @@ hipError_t launch_select(xp_handle* h, int batch, int pass, int K, uint32_t flag
 // truncated sampling (xp_filter.hip)
 hipError_t launch_filter_params(xp_handle* h, int batch, const uint8_t* temp, const int32_t* top_k,
                                 const float* top_p, hipStream_t st);
+int target_units(int V);      // vocabulary units of a target row
 hipError_t launch_fsample(xp_handle* h, int batch, int pass, uint32_t flags,
                           const int32_t* seed_ids, const float* u_draft, hipStream_t st);
 hipError_t launch_vfilter(xp_handle* h, int batch, const int32_t* draft, const float* tl,

@@ -203,6 +203,7 @@ __global__ __launch_bounds__(1024) void k_vresid(
   const int u = blockIdx.x * NW + wave;
   const int b = blockIdx.y * 16 + (lane & 15);
   const bool act = b < batch && temp != nullptr && temp[b] != 0;
+  if (__ballot(act) == 0) return;                 // all greedy or truncated: no mass is read
   const float it = invT[act ? b : 0];
   const int k = act ? vpos[b] : 0;
   const bool resid = act && k < B;

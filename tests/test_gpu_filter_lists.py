@@ -1,0 +1,45 @@
+"""Truncated sampling where its candidate list begins and ends, against the
+fp64 oracle (needs an MI355X): top-k of 1, at and beyond the number of
+vocabulary units, at and beyond the list's limit (which fall back to the
+general way), ties that overflow the list, and top-p alone and inside top-k, on
+the one-block stream, the GEMM and the fp32 kernels."""
+import numpy as np
+import pytest
+
+from _parity import custom_problem, make_refiner, run_device, upload
+from test_gpu_filter import _check
+
+pytestmark = pytest.mark.gpu
+
+STRESS = dict(W_e=1.0, W_r=0.3, L=0.3, W_in=0.08, W_1=0.08, W_2=0.06)
+
+
+# V = 20011: 1251 tiles, 1256 Read units of one tile, 314 LM-head GEMM units (or
+# 256 of the stream) and 313 target units, so k = 313, 314 and 1256 end the list
+# in one kernel and not in another; 1024 is the list's largest k
+@pytest.mark.parametrize("dtype,B,batch", [("bf16", 5, 2), ("bf16", 6, 8), ("f32", 5, 4)])
+@pytest.mark.parametrize("ks", [[1, 2, 255, 256], [257, 313, 314, 315],
+                                [1023, 1024, 1025, 1256], [1257, 20010, 0, 64]])
+def test_top_k_limits(dtype, B, batch, ks):
+    ks = (ks * batch)[:batch]
+    ps = [1.0, 0.9, 0.6, 1.0, 0.3, 0.99, 1.0, 0.8][:batch]
+    print(f"top-k limits {dtype} B={B} batch={batch} k={ks} p={ps}", flush=True)
+    prob = custom_problem(dtype, H=256, V=20011, B=B, batch=batch, K=3, sigmas=STRESS,
+                          temp="sample", seed=60 + ks[0] + batch,
+                          tau=np.linspace(0.6, 1.4, batch), top_k=ks, top_p=ps)
+    ref, dev = make_refiner(prob), upload(prob)
+    run = _check(prob, ref, dev, max_excused=2)
+    again = run_device(ref, prob, dev, early_exit=True)
+    assert np.array_equal(again.ids, run.ids)
+
+
+# every logit equal: k tokens tie with all others, the list overflows, and the
+# top-p cut falls inside the tie
+@pytest.mark.parametrize("V,k,p", [(5003, 3, 1.0), (5003, 3, 0.25), (300, 7, 0.5), (17, 2, 0.5)])
+def test_ties_overflow(V, k, p):
+    print(f"ties V={V} k={k} p={p}", flush=True)
+    prob = custom_problem("bf16", H=256, V=V, B=4, batch=5, K=2,
+                          sigmas=dict(W_lm=0.0, W_r=0.0), temp="sample", seed=90 + V % 50,
+                          top_k=k, top_p=p)
+    ref, dev = make_refiner(prob), upload(prob)
+    _check(prob, ref, dev, max_excused=0)
