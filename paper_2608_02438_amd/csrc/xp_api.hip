@@ -109,7 +109,10 @@ extern "C" xp_status xp_create(const xp_weights* w, int32_t max_batch, xp_handle
   }
   h->cus = cus > 0 ? cus : 256;
   h->lm_chunks = h->ntiles < h->cus ? h->ntiles : h->cus;
-  const int rw = (h->ntiles + kReadWaves - 1) / kReadWaves;
+  // four tiles per workgroup at least: a small vocabulary spreads over more CUs
+  // (with a tile for each of a workgroup's waves, 64 tiles sat on 8 CUs, each
+  // reading 128 KB of W_r by itself), some waves' units being empty
+  const int rw = (h->ntiles + 3) / 4;
   h->read_wgs = rw < h->cus ? rw : h->cus;
   h->read_units = h->read_wgs * kReadWaves;
   // the temperature-1 selection scans at most 4096 units per position and

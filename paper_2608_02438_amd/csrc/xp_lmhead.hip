@@ -6,6 +6,8 @@
 //
 // W_lm is streamed exactly once per 16-position block; the 16 positions'
 // activations stay on chip (LDS or registers) for the whole kernel.
+#include <type_traits>
+
 #include "xp_internal.h"
 
 namespace xp {
@@ -445,6 +447,211 @@ __global__ __launch_bounds__(1024) void k_lmhead_sk(
 }
 
 // ---------------------------------------------------------------------------
+// A1 in fp32 for more than one block.  The kernels above read W_lm once per 16
+// positions (33 positions of V = 33001, H = 2048: 270 MB three times, 208 us, now 94; 128
+// positions of V = 40000: 613 -> 269 us);
+// here a workgroup takes P blocks at once.  Its unit's tiles go in groups of at
+// most 12 - P; k advances 32 per stage through a ring of six 24 KB LDS stages
+// (the group's W rows and the blocks' h rows, 128 bytes each) filled by
+// global_load_lds, two 1 KB loads of whole lines per loading wave.  The (tile,
+// block) products of the group are dealt to the 16 waves, four per SIMD so that
+// one wave's operand reads overlap the others' matrix operations.  At P = 3 the matrix
+// operations (157 TFLOP/s at most) and the stream of W_lm cost about the same.
+// Row r's 16-byte chunk c sits at chunk c ^ ((r / 2) mod 8) of its 128 bytes:
+// 16 rows' reads of one chunk meet 16 different bank groups.
+// Sums: per product a chain over each k slice of the kernels above (their
+// wave's share), the slices added in order: the same fp32 values bit for bit.
+// ---------------------------------------------------------------------------
+constexpr int kFWaves32 = 16, kFLoaders = 12, kFLoads = 2, kFStages = 6;
+constexpr int kFSlots = kFLoaders * kFLoads * 64;      // 16-byte slots of a stage
+constexpr int kFItems = 32;                            // most products of a group
+
+template <int P>
+__global__ __launch_bounds__(kFWaves32 * kWave) void k_lmhead_f32(
+    const float* __restrict__ W, const float* __restrict__ X, int V, int H, int M, int ntiles,
+    int U, int slice, float* __restrict__ S, int Ms, uint64_t* __restrict__ keys,
+    Stat* __restrict__ stats, const uint8_t* __restrict__ temp, int B,
+    const float* __restrict__ invT) {
+  constexpr int TC = 12 - P;                           // tiles of a group
+  constexpr int NI = (TC * P + kFWaves32 - 1) / kFWaves32;
+  static_assert(16 * (TC + P) == 8 * kFLoaders * kFLoads, "rows of a stage");
+  static_assert(TC * P <= kFItems && NI == 2, "products of a group");
+  __shared__ u32x4 ring[kFStages * kFSlots];
+  __shared__ uint64_t kk[kFItems][kTile];
+  __shared__ Stat ss[kFItems][kTile];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, g = lane >> 4;
+  const int u = blockIdx.x, p0 = blockIdx.y * (kTile * P);
+  const int tlo = unit_tile_lo(u, ntiles, U), n = unit_tile_lo(u + 1, ntiles, U) - tlo;   // n >= 1
+  const int ng = (n + TC - 1) / TC, tpg = (n + ng - 1) / ng;
+  const int nk = H / 32, nst = ng * nk;
+
+  // this wave's loads: stage rows 8 (kFLoads wave + j) + lane / 8
+  const float* src[kFLoads];
+  auto aim = [&](int grp) {                            // at group grp, k 0
+#pragma unroll
+    for (int j = 0; j < kFLoads; ++j) {
+      const int r = 8 * (kFLoads * (wave < kFLoaders ? wave : 0) + j) + (lane >> 3);
+      const int ch = (lane & 7) ^ ((r >> 1) & 7);
+      const float* row;
+      if (r < 16 * TC) {
+        int t = grp * tpg + (r >> 4);
+        const int te = (grp + 1) * tpg < n ? (grp + 1) * tpg : n;
+        t = t < te ? t : te - 1;
+        int v = (tlo + t) * kTile + (r & 15);
+        v = v < V ? v : V - 1;
+        row = W + (size_t)v * H;
+      } else {
+        const int p = p0 + r - 16 * TC;
+        row = X + (size_t)(p < M ? p : M - 1) * H;
+      }
+      src[j] = row + 4 * ch;
+    }
+  };
+  int i_grp = 0, i_k = 0, i_slot = 0;
+  auto issue = [&]() {                                 // past the end the last stage again
+    if (wave >= kFLoaders) return;                     // wave-uniform
+#pragma unroll
+    for (int j = 0; j < kFLoads; ++j)
+      lds_dma16(src[j], &ring[i_slot * kFSlots + 64 * (kFLoads * wave + j)]);
+    i_slot = i_slot + 1 == kFStages ? 0 : i_slot + 1;
+    if (i_k + 1 < nk) {
+      ++i_k;
+#pragma unroll
+      for (int j = 0; j < kFLoads; ++j) src[j] += 32;
+    } else if (i_grp + 1 < ng) {
+      i_k = 0;
+      aim(++i_grp);
+    }
+  };
+
+  // product i of this wave: item wave + 8 i = tile P + block
+  int tile[NI], blk[NI];
+  bool pact[NI], samp[NI];
+  float pit[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int item = wave + kFWaves32 * i;
+    tile[i] = item / P;
+    blk[i] = item - tile[i] * P;
+    const int p = p0 + kTile * blk[i] + li, pc = p < M ? p : M - 1;
+    pact[i] = p < M;
+    samp[i] = pact[i] && load_flag(temp, pc / B, X) != 0;
+    pit[i] = invT[pc / B];
+  }
+#pragma unroll
+  for (int i = 0; i < NI; ++i) asm volatile("" ::"v"(pit[i]));
+  asm volatile("" ::: "memory");
+  aim(0);
+#pragma unroll
+  for (int q = 0; q < kFStages - 1; ++q) issue();
+
+  floatx4 acc[NI], tot[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) acc[i] = tot[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  uint64_t best = kKeyMin;                             // thread < 16 P: its position's
+  Stat st = stat_empty();
+  int cnt = 0, k = 0, grp = 0, slot = 0;
+  constexpr int kPend = kFLoads * (kFStages - 2);
+  for (int q = 0; q < nst; ++q) {
+    // stage q has landed for this wave, then for all; and every wave is done
+    // with stage q - 1, whose slot the next loads take
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070 | (kPend & 15) | ((kPend >> 4) << 14));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    issue();
+    const int gt = grp * tpg, nt = gt + tpg < n ? tpg : n - gt, nit = nt * P;
+    const u32x4* stage = ring + slot * kFSlots;
+    slot = slot + 1 == kFStages ? 0 : slot + 1;
+    // this wave's products of the group, all their operands read before the
+    // first operation and their chains interleaved
+    auto products = [&](auto cn) {
+      constexpr int N = cn;
+      u32x4 fa[2][N], fb[2][N];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const int c = (4 * ks + g) ^ ((li >> 1) & 7);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          fa[ks][i] = stage[(16 * tile[i] + li) * 8 + c];
+          fb[ks][i] = stage[(16 * (TC + blk[i]) + li) * 8 + c];
+        }
+      }
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < N; ++i)
+            acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(fa[ks][i][e]),
+                                                          __uint_as_float(fb[ks][i][e]), acc[i], 0,
+                                                          0, 0);
+        if (++cnt == slice) {
+          cnt = 0;
+#pragma unroll
+          for (int i = 0; i < N; ++i) {
+            tot[i] += acc[i];
+            acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+          }
+        }
+      }
+    };
+    const int mine = (nit - wave + kFWaves32 - 1) / kFWaves32;   // wave-uniform
+    if (mine >= NI)
+      products(std::integral_constant<int, NI>{});
+    else if (mine == 1)
+      products(std::integral_constant<int, 1>{});
+    else
+      cnt = (cnt + 2) % slice;
+    if (++k == nk) {                                   // the group's tiles are done
+      k = 0;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        if (wave + kFWaves32 * i < nit) {
+          const int row0 = (tlo + gt + tile[i]) * kTile + 4 * g;
+          const int p = p0 + kTile * blk[i] + li;
+          if (pact[i]) *reinterpret_cast<floatx4*>(S + s_index(p, row0, Ms)) = tot[i];
+          uint64_t key = kKeyMin;
+          float x[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const bool v = pact[i] && row0 + e < V;
+            if (v && !samp[i]) key = umax64(key, argmax_key(tot[i][e], (uint32_t)(row0 + e)));
+            x[e] = v && samp[i] ? tot[i][e] * pit[i] : -INFINITY;
+          }
+          Stat sv = stat_add4(stat_empty(), x[0], x[1], x[2], x[3]);
+#pragma unroll
+          for (int m = 16; m < 64; m <<= 1) {
+            key = umax64(key, shfl_xor_u64(key, m));
+            const Stat o{__shfl_xor(sv.m, m, kWave), __shfl_xor(sv.s, m, kWave)};
+            sv = stat_merge(sv, o);
+          }
+          if (lane < 16) {
+            kk[wave + kFWaves32 * i][lane] = key;
+            ss[wave + kFWaves32 * i][lane] = sv;
+          }
+        }
+        tot[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+      }
+      lds_barrier();
+      if (threadIdx.x < kTile * P) {
+        for (int t = 0; t < nt; ++t) {
+          best = umax64(best, kk[t * P + (threadIdx.x >> 4)][threadIdx.x & 15]);
+          st = stat_merge(st, ss[t * P + (threadIdx.x >> 4)][threadIdx.x & 15]);
+        }
+      }
+      ++grp;
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0x0070);                  // the loads past the end
+  if (threadIdx.x < kTile * P && p0 + (int)threadIdx.x < M) {
+    keys[(size_t)u * M + p0 + threadIdx.x] = best;
+    stats[(size_t)(p0 + threadIdx.x) * U + u] = st;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
 // Waves per workgroup and load units per wave for a hidden width H: the k
@@ -521,6 +728,27 @@ hipError_t launch_lmhead(xp_handle* h, int M, const void* hidden, const uint8_t*
     return launch_lmhead_gemm(h, M, hidden, temp, st);
   }
   h->lm_units_cur = h->lm_chunks;
+  // fp32 blocks together where a unit has tiles enough to deal to the waves (V =
+  // 8000, 33 positions: 64 us block by block, 47 together; V = 4000: 18 and 23)
+  if (h->dtype == XP_F32 && M > kTile && 2 * h->ntiles >= 3 * h->lm_chunks) {
+    int NU = 0, NW = 0;
+    if (!pick_lm_split(h->H, Mfma<float>::KU, &NU, &NW)) return hipErrorInvalidValue;
+    // blocks per workgroup: 2 to 4, spread evenly
+    const int nb = (M + kTile - 1) / kTile, ny = (nb + 3) / 4, P = (nb + ny - 1) / ny;
+    const dim3 grid(h->lm_chunks, (nb + P - 1) / P);
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, grid, dim3(kFWaves32 * kWave), 0, st, (const float*)h->W_lm,
+                         (const float*)hidden, h->V, h->H, M, h->ntiles, h->lm_chunks, NU,
+                         h->ws.s, M, h->ws.keys, h->ws.stats, temp, h->B, h->ws.invT);
+    };
+    if (P == 2)
+      go(k_lmhead_f32<2>);
+    else if (P == 3)
+      go(k_lmhead_f32<3>);
+    else
+      go(k_lmhead_f32<4>);
+    return hipGetLastError();
+  }
   if (h->dtype == XP_BF16) return launch_lmhead_t<uint16_t>(h, M, hidden, temp, st);
   return launch_lmhead_t<float>(h, M, hidden, temp, st);
 }

@@ -47,15 +47,15 @@ __device__ __forceinline__ void put_rows(float* dst, size_t at, const floatx4& v
 // last tile, which hits in L2).  Workgroups merge their waves' argmax keys;
 // sampled rows write one (max, sum) per wave unit.
 // ---------------------------------------------------------------------------
-template <typename T>
 __global__ __launch_bounds__(kReadWaves * kWave) void k_read(
-    const T* __restrict__ W, const T* __restrict__ Z, const float* __restrict__ S, int Ms, int V,
+    const uint16_t* __restrict__ W, const uint16_t* __restrict__ Z, const float* __restrict__ S, int Ms, int V,
     int M, int ntiles, int U, uint64_t* __restrict__ keys, Stat* __restrict__ stats,
     const uint8_t* __restrict__ temp, int B, LogitRows rows, const int32_t* __restrict__ ctrl,
     int skip_when_done, const float* __restrict__ invT) {
   if (skip_when_done && ctrl[1]) return;          // every sequence is at its fixed point
+  using T = uint16_t;
   constexpr int NU = ReadTile<T>::NU;
-  constexpr int NR = sizeof(T) == 2 ? 5 : 2;      // resident tiles per wave (32 / 64 VGPRs each)
+  constexpr int NR = 5;                           // resident tiles per wave (32 VGPRs each)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int u = blockIdx.x * kReadWaves + wave, p0 = blockIdx.y * kTile;
   const int tlo = unit_tile_lo(u, ntiles, U), thi = unit_tile_lo(u + 1, ntiles, U);
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read(
   __shared__ uint64_t kred[kReadWaves][kTile];
   // per-wave transpose tile (16 rows x 32 chunks, chunk XOR-swizzled by row:
   // conflict-free for the row-contiguous writes and the MFMA-order reads)
-  __shared__ u32x4 tbuf[sizeof(T) == 2 ? kReadWaves : 1][16 * 32];
+  __shared__ u32x4 tbuf[kReadWaves][16 * 32];
 
   const int p = p0 + (lane & 15);
   const bool act = p < M;
@@ -137,87 +137,55 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read(
     }
   };
 
-  if constexpr (sizeof(T) == 2) {
-    if (n >= 1 && n <= NR) {
-      // Line-complete loads: instruction i of a tile reads its rows 2i, 2i+1
-      // (1 KB contiguous, non-temporal); each tile is then transposed through
-      // the wave's LDS tile into the MFMA operand order of ReadTile::load_w,
-      // so the chain sees exactly the operands of the rescans.
-      // Issue order = use order (z, s, then the tiles): the vector-memory
-      // counter drains in order, so tile j waits only for the loads before it.
-      u32x4 a[NR][8];
-      floatx4 c[NR];
-      const int lrow = lane >> 5, lch = lane & 31;
-      const int tv = load_flag(temp, pc / B, S);
-      load_z();
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int j = 0; j < NR; ++j) c[j] = load_s(tlo + (j < n ? j : n - 1));
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int j = 0; j < NR; ++j) {
-        const int t = tlo + (j < n ? j : n - 1);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          int row = t * kTile + 2 * i + lrow;
-          row = row < V ? row : V - 1;
-          a[j][i] = ld16_nt(W + (size_t)row * 256 + lch * 8);
-        }
-      }
-      sample = act && tv != 0;
-      any_sample = __ballot(sample) != 0;
-      put_z();
-      lds_barrier();
-      fetch_z();
-      u32x4* tb = tbuf[wave];
-      const int li = lane & 15, g = lane >> 4;
-#pragma unroll
-      for (int j = 0; j < NR; ++j) {
-        if (j < n) {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const int row = 2 * i + lrow;
-            tb[row * 32 + (lch ^ row)] = a[j][i];
-          }
-          wave_lds_order();
-          u32x4 m[NU];
-#pragma unroll
-          for (int i = 0; i < NU; ++i) m[i] = tb[li * 32 + ((4 * i + g) ^ li)];
-          wave_lds_order();
-          epilogue(chain_lds(m, c[j]), tlo + j);
-        }
-      }
-    } else {
-      load_z();
-      const int tv = load_flag(temp, pc / B, S);
-      sample = act && tv != 0;
-      any_sample = __ballot(sample) != 0;
-      put_z();
-      __syncthreads();
-      fetch_z();
-      u32x4 a[NU];
-      for (int t = tlo; t < thi; ++t) {
-        ReadTile<T>::load_w(W, V, t, lane, a);
-        epilogue(chain_lds(a, load_s(t)), t);
-      }
-    }
-  } else if (n >= 1 && n <= NR) {
-    u32x4 a[NR][NU];
+  if (n >= 1 && n <= NR) {
+    // Line-complete loads: instruction i of a tile reads its rows 2i, 2i+1
+    // (1 KB contiguous, non-temporal); each tile is then transposed through
+    // the wave's LDS tile into the MFMA operand order of ReadTile::load_w,
+    // so the chain sees exactly the operands of the rescans.
+    // Issue order = use order (z, s, then the tiles): the vector-memory
+    // counter drains in order, so tile j waits only for the loads before it.
+    u32x4 a[NR][8];
     floatx4 c[NR];
-#pragma unroll
-    for (int j = 0; j < NR; ++j) ReadTile<T>::load_w(W, V, tlo + (j < n ? j : n - 1), lane, a[j]);
+    const int lrow = lane >> 5, lch = lane & 31;
+    const int tv = load_flag(temp, pc / B, S);
+    load_z();
+    asm volatile("" ::: "memory");
 #pragma unroll
     for (int j = 0; j < NR; ++j) c[j] = load_s(tlo + (j < n ? j : n - 1));
-    load_z();
-    const int tv = load_flag(temp, pc / B, S);
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+      const int t = tlo + (j < n ? j : n - 1);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        int row = t * kTile + 2 * i + lrow;
+        row = row < V ? row : V - 1;
+        a[j][i] = ld16_nt(W + (size_t)row * 256 + lch * 8);
+      }
+    }
     sample = act && tv != 0;
     any_sample = __ballot(sample) != 0;
     put_z();
-    __syncthreads();
+    lds_barrier();
     fetch_z();
+    u32x4* tb = tbuf[wave];
+    const int li = lane & 15, g = lane >> 4;
 #pragma unroll
-    for (int j = 0; j < NR; ++j)
-      if (j < n) epilogue(chain_lds(a[j], c[j]), tlo + j);
+    for (int j = 0; j < NR; ++j) {
+      if (j < n) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int row = 2 * i + lrow;
+          tb[row * 32 + (lch ^ row)] = a[j][i];
+        }
+        wave_lds_order();
+        u32x4 m[NU];
+#pragma unroll
+        for (int i = 0; i < NU; ++i) m[i] = tb[li * 32 + ((4 * i + g) ^ li)];
+        wave_lds_order();
+        epilogue(chain_lds(m, c[j]), tlo + j);
+      }
+    }
   } else {
     load_z();
     const int tv = load_flag(temp, pc / B, S);
@@ -243,6 +211,141 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read(
   if (lane < 16) kred[wave][lane] = best;
   __syncthreads();
   if (threadIdx.x < kTile) {
+    uint64_t b = kKeyMin;
+    for (int w = 0; w < kReadWaves; ++w) b = umax64(b, kred[w][threadIdx.x]);
+    const int pp = p0 + threadIdx.x;
+    if (pp < M) keys[(size_t)blockIdx.x * M + pp] = b;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// A7 in fp32: one wave per unit, PB 16-position blocks per workgroup (their z in
+// LDS), the next W_r tile in flight while one multiplies.  A block at a time
+// (the form before) read W_r once per 16 positions: 35.6 us a pass at 33
+// positions of V = 33001, bound by those reads and by one chain of dependent
+// matrix operations per wave; PB interleaved chains share every tile.  Each
+// chain is ReadTile::chain's, so the logits are those of the rescans.
+// ---------------------------------------------------------------------------
+template <int PB>
+__global__ __launch_bounds__(kReadWaves * kWave) void k_read_f32(
+    const float* __restrict__ W, const float* __restrict__ Z, const float* __restrict__ S, int Ms,
+    int V, int M, int ntiles, int U, uint64_t* __restrict__ keys, Stat* __restrict__ stats,
+    const uint8_t* __restrict__ temp, int B, LogitRows rows, const int32_t* __restrict__ ctrl,
+    int skip_when_done, const float* __restrict__ invT) {
+  if (skip_when_done && ctrl[1]) return;          // every sequence is at its fixed point
+  using RT = ReadTile<float>;
+  constexpr int NU = RT::NU;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int u = blockIdx.x * kReadWaves + wave, p0 = blockIdx.y * (kTile * PB);
+  const int tlo = unit_tile_lo(u, ntiles, U), thi = unit_tile_lo(u + 1, ntiles, U);
+  const int tl = thi > tlo ? tlo : (tlo < ntiles ? tlo : ntiles - 1);   // an empty unit loads a tile it drops
+  __shared__ u32x4 zl[PB][NU][64];
+  __shared__ uint64_t kred[kReadWaves][PB * kTile];
+
+  u32x4 a[NU], an[NU];
+  floatx4 c[PB], cn[PB];
+  int pc[PB];
+  bool act[PB], sample[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) {
+    const int p = p0 + kTile * pb + (lane & 15);
+    act[pb] = p < M;
+    pc[pb] = act[pb] ? p : M - 1;
+  }
+  auto load = [&](int t, u32x4 (&w)[NU], floatx4 (&s4)[PB]) {
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb)
+      s4[pb] = *reinterpret_cast<const floatx4*>(S + s_index(pc[pb], t * kTile + 4 * (lane >> 4), Ms));
+    RT::load_w(W, V, t, lane, w);
+  };
+  // z fragments of the blocks, 16-byte chunks in turn over the threads
+  constexpr int kZPer = PB * NU * 64 / (kReadWaves * kWave);
+  u32x4 zv[kZPer];
+#pragma unroll
+  for (int j = 0; j < kZPer; ++j) {
+    const int ch = threadIdx.x + kReadWaves * kWave * j;
+    const int pb = ch / (NU * 64), zi = (ch / 64) % NU, zlane = ch % 64;
+    const int zp = p0 + kTile * pb + (zlane & 15);
+    zv[j] = ld16(Z + (size_t)(zp < M ? zp : M - 1) * 256 + (zlane >> 4) * RT::EPB + zi * RT::KU);
+  }
+  asm volatile("" ::: "memory");
+  load(tl, a, c);
+  asm volatile("" ::: "memory");
+  uint64_t best[PB];
+  Stat st[PB];
+  float pit[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) {
+    sample[pb] = act[pb] && load_flag(temp, pc[pb] / B, S) != 0;
+    pit[pb] = invT[pc[pb] / B];
+    best[pb] = kKeyMin;
+    st[pb] = stat_empty();
+  }
+#pragma unroll
+  for (int j = 0; j < kZPer; ++j) {
+    const int ch = threadIdx.x + kReadWaves * kWave * j;
+    const int zp = p0 + kTile * (ch / (NU * 64)) + (ch & 15);
+    zl[ch / (NU * 64)][(ch / 64) % NU][ch % 64] = zp < M ? zv[j] : u32x4{0u, 0u, 0u, 0u};
+  }
+  lds_barrier();
+  auto tile = [&](const u32x4 (&w)[NU], const floatx4 (&s4)[PB], int t) {
+    floatx4 acc[PB];
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) acc[pb] = act[pb] ? s4[pb] : floatx4{0.f, 0.f, 0.f, 0.f};
+    // z one load unit ahead (all of it at once would not fit the registers)
+    u32x4 z[2][PB];
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) z[0][pb] = zl[pb][0][lane];
+#pragma unroll
+    for (int i = 0; i < NU; ++i) {
+      if (i + 1 < NU) {
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) z[(i + 1) & 1][pb] = zl[pb][i + 1][lane];
+      }
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) acc[pb] = Mfma<float>::mma(w[i], z[i & 1][pb], acc[pb]);
+    }
+    const int row0 = t * kTile + 4 * (lane >> 4);
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+      const int p = p0 + kTile * pb + (lane & 15);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool v = act[pb] && row0 + i < V;
+        const uint64_t key = umax64(best[pb], argmax_key(acc[pb][i], (uint32_t)(row0 + i)));
+        best[pb] = v && !sample[pb] ? key : best[pb];
+        if (sample[pb] && v) st[pb] = stat_merge(st[pb], Stat{acc[pb][i] * pit[pb], 1.f});
+      }
+      if (act[pb] && rows.out) put_rows(rows.out, (size_t)p * V + row0, acc[pb], row0, V, rows.vec);
+      if (act[pb] && rows.lf && rows.filt[pc[pb] / B])
+        put_rows(rows.lf, (size_t)p * V + row0, acc[pb], row0, V, rows.vec);
+    }
+  };
+  if (thi - tlo == 1) {
+    tile(a, c, tlo);
+  } else {
+    for (int t = tlo; t < thi; t += 2) {
+      load(t + 1 < thi ? t + 1 : thi - 1, an, cn);
+      tile(a, c, t);
+      if (t + 1 >= thi) break;
+      load(t + 2 < thi ? t + 2 : thi - 1, a, c);
+      tile(an, cn, t + 1);
+    }
+  }
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) {
+#pragma unroll
+    for (int m = 16; m < 64; m <<= 1) {
+      best[pb] = umax64(best[pb], shfl_xor_u64(best[pb], m));
+      const Stat o{__shfl_xor(st[pb].m, m, kWave), __shfl_xor(st[pb].s, m, kWave)};
+      st[pb] = stat_merge(st[pb], o);
+    }
+    if (lane < 16 && sample[pb]) stats[(size_t)(p0 + kTile * pb + lane) * U + u] = st[pb];
+    if (lane < 16) kred[wave][kTile * pb + lane] = best[pb];
+  }
+  __syncthreads();
+  if (threadIdx.x < PB * kTile) {
     uint64_t b = kKeyMin;
     for (int w = 0; w < kReadWaves; ++w) b = umax64(b, kred[w][threadIdx.x]);
     const int pp = p0 + threadIdx.x;
@@ -615,16 +718,34 @@ hipError_t launch_read(xp_handle* h, int batch, uint32_t flags, const uint8_t* t
 #undef XP_RM
     return hipGetLastError();
   }
-  if (h->dtype == XP_BF16)
-    hipLaunchKernelGGL((k_read<uint16_t>), grid, block, 0, st, (const uint16_t*)h->W_r,
+  if (h->dtype == XP_BF16) {
+    hipLaunchKernelGGL(k_read, grid, block, 0, st, (const uint16_t*)h->W_r,
                        (const uint16_t*)h->ws.z, h->ws.s, M, h->V, M, h->ntiles,
                        h->read_units, h->ws.keys, h->ws.stats, temp, h->B, rows, h->ws.ctrl,
                        skip, h->ws.invT);
-  else
-    hipLaunchKernelGGL((k_read<float>), grid, block, 0, st, (const float*)h->W_r,
-                       (const float*)h->ws.z, h->ws.s, M, h->V, M, h->ntiles, h->read_units,
-                       h->ws.keys, h->ws.stats, temp, h->B, rows, h->ws.ctrl, skip,
-                       h->ws.invT);
+    return hipGetLastError();
+  }
+  // fp32: up to 4 position blocks per workgroup, as many as make one workgroup
+  // per CU (its registers allow no second one): V = 33001 at 33 positions takes
+  // three (36 -> 26 us a pass), a vocabulary of few workgroups one each
+  const int nb = (M + kTile - 1) / kTile;
+  int PB = (h->read_wgs * nb + h->cus - 1) / h->cus;
+  PB = PB < 4 ? PB : 4;
+  PB = PB < nb ? PB : nb;
+  const int ny = (nb + PB - 1) / PB;
+  PB = (nb + ny - 1) / ny;
+  grid = dim3(h->read_wgs, (nb + PB - 1) / PB);
+#define XP_RF(PP)                                                                             \
+  hipLaunchKernelGGL((k_read_f32<PP>), grid, block, 0, st, (const float*)h->W_r,               \
+                     (const float*)h->ws.z, h->ws.s, M, h->V, M, h->ntiles, h->read_units,     \
+                     h->ws.keys, h->ws.stats, temp, h->B, rows, h->ws.ctrl, skip, h->ws.invT)
+  switch (PB) {
+    case 1: XP_RF(1); break;
+    case 2: XP_RF(2); break;
+    case 3: XP_RF(3); break;
+    default: XP_RF(4);
+  }
+#undef XP_RF
   return hipGetLastError();
 }
 
