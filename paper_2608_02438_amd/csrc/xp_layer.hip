@@ -21,19 +21,21 @@
 //                 tiles are fewer than the CUs)
 //   k_qkrope      QK-norm and RoPE of every q and k head, v to bf16 (adding
 //                 the q/k/v projection's split-K slabs)
-//   k_attn        split-KV block attention: a workgroup takes a chunk of
-//                 64-key sub-chunks of one KV head for 16 block positions, one
-//                 wave per query head of the group, with an online softmax;
-//                 each sub-chunk's K and V (transposed) staged in LDS while the
-//                 next one loads; S = K Q^T and O = P V on the matrix cores
-//   k_attn_comb   merges the chunks of every query row in chunk order
+//   k_attn        split-KV block attention: a workgroup takes an equal share of
+//                 all 64-key sub-chunks of the call, one wave per query head of
+//                 the group and 16 block positions, with an online softmax; each
+//                 sub-chunk's K and V staged in LDS while the next ones load; S =
+//                 K Q^T and O = P V on the matrix cores
+//   k_attn_comb   merges the parts of every query row in order
 //   k_splitk_sum  the down projection's split-K slabs + x1, to h
 // Every reduction runs in a fixed order, so two runs give identical bits.
 #include <stdarg.h>
 #include <stdio.h>
 
 #include <algorithm>
+#include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "xp_internal.h"
 
@@ -41,8 +43,9 @@ namespace xp {
 
 constexpr int kLinWaves = 8;        // k-split of k_linear
 constexpr int kLinMaxStream = 64;   // positions up to which the projections stream
-constexpr int kAttnWgs = 1024;      // attention workgroups aimed at per call
+constexpr int kAttnWgs = 512;       // attention workgroups of a call at most (256 CUs x 2)
 constexpr int kHd = 128;            // head_dim (the only one built)
+constexpr int kSub = 64;            // keys per attention sub-chunk (one LDS stage)
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -426,30 +429,55 @@ __global__ __launch_bounds__(kGsWaves * kWave) void k_gemv_sk(
 }
 
 // ---------------------------------------------------------------------------
-// QK-norm + RoPE: one workgroup per position m; wave w takes the head slots
-// w, w + 4, ...: slots [0, nh) are the q heads, [nh, nh + nkv) the k heads,
+// QK-norm + RoPE: gridDim.y workgroups per position m (more for few positions,
+// where a wave's slots one after the other are all the time there is); wave w of
+// workgroup y takes the head slots 4 y + w, + 4 gridDim.y, ...: slots [0, nh) are the q heads, [nh, nh + nkv) the k heads,
 // [nh + nkv, nh + 2 nkv) the v heads (converted only).  Lane l holds elements
-// l and l + 64, the rotate-half pair of frequency l; the angle (taken in
-// double) depends on the position and l only, so each wave forms its cosine
+// l and l + 64, the rotate-half pair of frequency l; the angle (taken in double,
+// lt = log2 theta) depends on the position and l only, so each wave forms its cosine
 // and sine once for all its slots.  The row is P_0 + ... + P_{S-1}
 // (P_s = qkv + s slab, added in that order; S = 1: the projection itself).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_qkrope(
     const float* __restrict__ qkv, int S, size_t slab, int ldq, int B, int nh, int nkv,
     const int32_t* __restrict__ ctx_len, int Cmax, const uint16_t* __restrict__ gq,
-    const uint16_t* __restrict__ gk, float eps, float theta, uint16_t* __restrict__ qn,
-    uint16_t* __restrict__ kb, uint16_t* __restrict__ vb) {
+    const uint16_t* __restrict__ gk, float eps, double lt, uint16_t* __restrict__ qn,
+    uint16_t* __restrict__ kb, uint16_t* __restrict__ vb, int batch, int32_t* __restrict__ pre) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m = blockIdx.x;
+  // the last workgroup's last wave also lays out the attention's work: pre[b] =
+  // the 64-key sub-chunks of the sequences before b (of one KV head), pre[batch]
+  // all of them
+  if (m == (int)gridDim.x - 1 && blockIdx.y == 0 && wave == 3) {
+    int sum = 0;
+    for (int b0 = 0; b0 < batch; b0 += kWave) {
+      const int b = b0 + lane;
+      int C = b < batch ? ctx_len[b] : 0;
+      C = C < 0 ? 0 : (C > Cmax ? Cmax : C);
+      int n = b < batch ? (C + B + kSub - 1) / kSub : 0;
+#pragma unroll
+      for (int off = 1; off < kWave; off <<= 1) {
+        const int y = __shfl_up(n, off, kWave);
+        if (lane >= off) n += y;
+      }
+      if (b < batch) pre[b + 1] = sum + n;
+      sum += __shfl(n, kWave - 1, kWave);
+    }
+    if (lane == 0) pre[0] = 0;
+  }
   const int nslots = nh + 2 * nkv;
   int C = ctx_len[m / B];
   C = C < 0 ? 0 : (C > Cmax ? Cmax : C);
+  // the angle in half turns, pos theta^(-2 l / hd) / pi, and its sine and cosine
+  // in double (exp2 and sincospi cost a third of pow, sin and cos)
   const double pos = (double)(C + m % B);
-  const double ang = pos * pow((double)theta, -2.0 * (double)lane / (double)kHd);
-  const float cs = (float)cos(ang), sn = (float)sin(ang);
+  const double half = pos * (exp2(-2.0 * (double)lane / (double)kHd * lt) * 0.31830988618379067154);
+  double sd, cd;
+  sincospi(half, &sd, &cd);
+  const float cs = (float)cd, sn = (float)sd;
   const float gq0 = bf16_to_f32(gq[lane]), gq1 = bf16_to_f32(gq[lane + 64]);
   const float gk0 = bf16_to_f32(gk[lane]), gk1 = bf16_to_f32(gk[lane + 64]);
-  for (int hs = wave; hs < nslots; hs += 4) {
+  for (int hs = 4 * blockIdx.y + wave; hs < nslots; hs += 4 * gridDim.y) {
     const float* src = qkv + (size_t)m * ldq + (size_t)hs * kHd;
     float a = src[lane], b = src[lane + 64];
     for (int q = 1; q < S; ++q) {
@@ -475,11 +503,20 @@ __global__ __launch_bounds__(256) void k_qkrope(
 }
 
 // ---------------------------------------------------------------------------
-// Split-KV block attention, flash-decoding style.  Grid (chunk s, KV head,
-// sequence b); wave w is query head kvh * GRP + w % GRP for the block
-// positions 16 pb .. 16 pb + 15, pb = w / GRP (NPB position blocks), so the
-// group's query heads and the block's positions share every K and V byte
-// read.  A chunk is nsub sub-chunks of 64 keys, walked with an online softmax.
+// Split-KV block attention, flash-decoding style.  The call's work is the list
+// of all 64-key sub-chunks, sequence by sequence, KV head by KV head; workgroup
+// w takes the w-th of W equal shares of it, a part of one or of several
+// (sequence, KV head) segments, each part walked with an online softmax and
+// written as one partial (number w + segment: a step of either index at a
+// time).  So the workgroups carry the same load whatever the context lengths
+// (chunks of one length per sequence left the last workgroups of contexts of
+// 512 to 16384 keys running alone), and the partials are at most W + segments -
+// 1.  Bound by the loop's LDS reads, vector and matrix operations together more
+// than by HBM: batch 32 x 16 at 8192 keys 252 -> 204 us (5.3 TB/s), batch 64 x 32
+// at 512 .. 16384 keys 832 -> 581 us (3.8 TB/s), batch 8 x 16 at 4096 43 -> 32 us.  Wave w is query head kvh * GRP +
+// w % GRP for the block positions 16 pb .. 16 pb + 15, pb = w / GRP (NPB
+// position blocks), so the group's query heads and the block's positions share
+// every K and V byte read.
 // Key kk of sequence b is context key kk (kk < C) or block key kk - C
 // (C <= kk < C + B); keys from C + B on do not exist (their rows are loaded
 // as the last key's and masked).
@@ -503,14 +540,32 @@ __global__ __launch_bounds__(256) void k_qkrope(
 // rescaled by 2^(m_old - m_new).  Written per (chunk, query): O and l
 // relative to the chunk's final reference m, and m.
 // ---------------------------------------------------------------------------
-constexpr int kSub = 64;                       // keys per sub-chunk (one LDS stage)
 constexpr int kAttnSlots = 2 * kSub * kHd / 8; // 16-byte slots of a stage: K rows, then V rows
 
-typedef short v4i16 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint2 lds_read_tr16(const uint16_t* p) {   // p: an LDS address
-  const v4i16 r =
-      __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4i16*)p);
-  return __builtin_bit_cast(uint2, r);
+// Four pairs of transposing LDS reads (ds_read_b64_tr_b16), pair i at LDS byte
+// address a[i] and 16 rows (4096 bytes) on, and the wait for them.  The builtin
+// is not used: the compiler takes its read for a use of the global-to-LDS loads
+// in flight and waits for all of them (vmcnt(0)) before the first one of every
+// step, so that each sub-chunk's loads were waited for right after they were
+// issued.  The ring's own wait and barrier order these reads.
+__device__ __forceinline__ void lds_read_tr16x8(const uint32_t (&a)[4], u32x4 (&v)[4]) {
+  uint2 r[8];
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:4096\n\t"
+      "ds_read_b64_tr_b16 %2, %9\n\tds_read_b64_tr_b16 %3, %9 offset:4096\n\t"
+      "ds_read_b64_tr_b16 %4, %10\n\tds_read_b64_tr_b16 %5, %10 offset:4096\n\t"
+      "ds_read_b64_tr_b16 %6, %11\n\tds_read_b64_tr_b16 %7, %11 offset:4096\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]),
+        "=&v"(r[7])
+      : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
+      : "memory");
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = u32x4{r[2 * i].x, r[2 * i].y, r[2 * i + 1].x, r[2 * i + 1].y};
+}
+// the LDS byte address of p (in LDS)
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }
 
 // Waves of a workgroup: one per (query head of the group, position block),
@@ -518,17 +573,49 @@ __device__ __forceinline__ uint2 lds_read_tr16(const uint16_t* p) {   // p: an L
 // pair take keys 0..31 and 32..63 of every sub-chunk with their own running
 // maximum, sum and O, merged at the end), so that a CU holds enough waves to
 // hide each one's latency (with eight pairs the halves' extra registers cost
-// more than they hide: measured).  The LDS ring has NS = 2 stages (64 KB, two
-// workgroups per CU), 3 for 16 waves (96 KB, one workgroup per CU).
+// more than they hide: measured).
 __host__ __device__ constexpr int attn_halves(int grp, int npb) { return grp * npb <= 4 ? 2 : 1; }
 __host__ __device__ constexpr int attn_waves(int grp, int npb) {
   return grp * npb * attn_halves(grp, npb);
 }
+// Ring stages (32 KB each) and workgroups per CU: two workgroups of two stages,
+// or one of three: with 16 waves, and with the eight of the key halves, whose
+// one head-block pair in flight per wave leaves HBM latency to the ring (batch
+// 32 x 16, 8192 keys: 538 us a forward with one workgroup and three stages, 556
+// with two and two, 542 with one and five; batch 64 x 32: 1520 and 1476).
+__host__ __device__ constexpr int attn_cu_wgs(int grp, int npb) {
+  return attn_waves(grp, npb) >= 16 || grp * npb == 4 ? 1 : 2;
+}
+// Waves per SIMD that the registers must allow for that.
+__host__ __device__ constexpr int attn_occ(int grp, int npb) {
+  const int w = attn_waves(grp, npb) * attn_cu_wgs(grp, npb) / 4;
+  return w < 1 ? 1 : w;
+}
+// The equal shares of a call's pre_all * nkv sub-chunks over W workgroups (W0 at
+// most, and no empty share): share w is [first(w), first(w + 1)).
+struct AttnShare {
+  int64_t T;
+  int W;
+  __device__ __forceinline__ AttnShare(int pre_all, int nkv, int W0)
+      : T((int64_t)pre_all * nkv), W(T < W0 ? (int)T : W0) {}
+  // (32-bit divisions where they do: 64-bit ones are a long chain at the start of
+  // every workgroup)
+  __device__ __forceinline__ int64_t first(int w) const {
+    return T < kSmall ? (int64_t)((uint32_t)T * (uint32_t)w / (uint32_t)W) : T * w / W;
+  }
+  // the share that holds sub-chunk f
+  __device__ __forceinline__ int of(int64_t f) const {
+    return T < kSmall ? (int)((((uint32_t)f + 1) * (uint32_t)W - 1) / (uint32_t)T)
+                      : (int)(((f + 1) * W - 1) / T);
+  }
+  static constexpr int64_t kSmall = (int64_t)1 << 22;   // times kAttnWgs stays below 2^32
+};
+
 template <int GRP, int NPB>
 struct AttnShape {
   static constexpr int KH = attn_halves(GRP, NPB);
   static constexpr int W = attn_waves(GRP, NPB);
-  static constexpr int NS = W >= 16 ? 3 : 2;
+  static constexpr int NS = attn_cu_wgs(GRP, NPB) == 1 ? 3 : 2;
 };
 
 // The PER loads of one wave for the sub-chunk starting at key k0 into the
@@ -556,33 +643,30 @@ __device__ __forceinline__ void attn_issue(u32x4* stage, int wave, int lane, int
   }
 }
 
-// One sub-chunk of the wave's keys (tiles t0 .. t0 + NT - 1 of the stage at
-// Ks / Vs): S, the online softmax and O += P V.  Scores are kept in base-2
+// NT 16-key tiles of a stage (K rows at Ks, V rows at Vs, the first key kb0;
+// the rows start at a multiple of 16): S, the online softmax and O += P V.  Scores are kept in base-2
 // units (q.k / sqrt(hd) times log2 e), so every exponential is one exp2.
-template <int NT>
+// INT: every key of the sub-chunk is a context key (no mask).
+template <int NT, bool INT>
 __device__ __forceinline__ void attn_step(const u32x4* Ks, const uint16_t* Vs,
-                                          const u32x4 (&qf)[kHd / 32], int t0, int g, int li,
-                                          bool qv, bool interior, int kb0, int nkeys, int C,
-                                          int causal, int p, floatx4 (&o)[kHd / 16],
-                                          float& m_run, float& l_run) {
+                                          const u32x4 (&qf)[kHd / 32], int g, int li, int kb0, int nkeys, int C, int causal, int p, floatx4 (&o)[kHd / 16], float& m_run,
+                                          floatx4& l_run) {
   constexpr float kScale2 = 0.12751743082459868f;   // log2(e) / sqrt(128)
   floatx4 sc[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    const int kr = kTile * (t0 + t) + li;         // A operand: key kr, d 32 ks + 8 g ..
+    const int kr = kTile * t + li;                // A operand: key kr, d 32 ks + 8 g ..
     floatx4 acc{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < kHd / 32; ++ks)
       acc = Mfma<uint16_t>::mma(Ks[kr * 16 + ((4 * ks + g) ^ li)], qf[ks], acc);
-    if (interior) {                               // workgroup-uniform
-#pragma unroll
-      for (int i = 0; i < 4; ++i) sc[t][i] = qv ? acc[i] * kScale2 : -INFINITY;
-    } else {
+    sc[t] = acc;
+    if constexpr (!INT) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int key = kb0 + kTile * (t0 + t) + 4 * g + i;
-        const bool vis = qv && key < nkeys && (key < C || !causal || key - C <= p);
-        sc[t][i] = vis ? acc[i] * kScale2 : -INFINITY;
+        const int key = kb0 + kTile * t + 4 * g + i;
+        const bool vis = key < nkeys && (key < C || !causal || key - C <= p);
+        sc[t][i] = vis ? acc[i] : -INFINITY;
       }
     }
   }
@@ -596,73 +680,70 @@ __device__ __forceinline__ void attn_step(const u32x4* Ks, const uint16_t* Vs,
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int i = 0; i < 4; ++i) mt = fmaxf(mt, sc[t][i]);
-  mt = fmax_xor32(fmax_xor16(mt));
+  mt = fmax_xor32(fmax_xor16(mt)) * kScale2;
   const bool grow = __ballot(mt > m_run + kLazy) != 0;   // wave-uniform
   const float mref = grow ? fmaxf(m_run, mt) : m_run;
   // with no visible key yet (mref = -inf) every exponent below is -inf: 0
   const float mxs = mref == -INFINITY ? 0.f : mref;
-  // numerators as two bf16 parts (hi = bf16(e), lo = bf16(e - hi)); the
-  // sum is taken over the same parts
+  // numerators as two bf16 parts (hi = bf16(e), lo = bf16(e - hi)); l sums the
+  // same parts on the matrix cores, as one more column of V that holds ones
   uint32_t eh[NT][2], el[NT][2];
-  float lsum = 0.f;
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int i = 0; i < 4; i += 2) {
-      const float e0 = __builtin_amdgcn_exp2f(sc[t][i] - mxs);
-      const float e1 = __builtin_amdgcn_exp2f(sc[t][i + 1] - mxs);
+      const float e0 = __builtin_amdgcn_exp2f(fmaf(sc[t][i], kScale2, -mxs));
+      const float e1 = __builtin_amdgcn_exp2f(fmaf(sc[t][i + 1], kScale2, -mxs));
       const uint32_t h = pk_bf16(e0, e1);
-      const float h0 = __uint_as_float(h << 16), h1 = __uint_as_float(h & 0xFFFF0000u);
-      const uint32_t lo = pk_bf16(e0 - h0, e1 - h1);
-      const float l0 = __uint_as_float(lo << 16), l1 = __uint_as_float(lo & 0xFFFF0000u);
-      lsum += h0 + l0;
-      lsum += h1 + l1;
       eh[t][i / 2] = h;
-      el[t][i / 2] = lo;
+      el[t][i / 2] = pk_bf16(e0 - __uint_as_float(h << 16), e1 - __uint_as_float(h & 0xFFFF0000u));
     }
-  lsum = fadd_xor32(fadd_xor16(lsum));
   if (grow) {                                     // wave-uniform
     const float alpha = __builtin_amdgcn_exp2f(m_run - mxs);
-    l_run = l_run * alpha + lsum;
-    // O rows are queries 4 (l / 16) + i: their factors come from lanes 4 g + i
+    // O and l rows are queries 4 (l / 16) + i: their factors come from lanes 4 g + i
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float ai = __shfl(alpha, 4 * g + i, kWave);
+      l_run[i] *= ai;
 #pragma unroll
       for (int dt = 0; dt < kHd / 16; ++dt) o[dt][i] *= ai;
     }
-  } else {
-    l_run += lsum;
   }
   m_run = mref;
   // V reads: lane (g, li) supplies key row k0 + li / 4 (k0 = 32 u + 4 g,
   // then + 16), columns 16 dt + 4 (li % 4) .. + 3: chunk 2 dt + (li % 4) / 2,
   // half (li % 4) & 1
-  const int vr = li >> 2, vc = (li & 3) >> 1, vh = 4 * (li & 1);
+  const int r0 = 4 * g + (li >> 2), vc = (li & 3) >> 1;
+  const uint32_t va = lds_addr(Vs) + 256u * r0 + 8u * (li & 1);
 #pragma unroll
   for (int u = 0; u < NT / 2; ++u) {
     const u32x4 ph{eh[2 * u][0], eh[2 * u][1], eh[2 * u + 1][0], eh[2 * u + 1][1]};
     const u32x4 pl{el[2 * u][0], el[2 * u][1], el[2 * u + 1][0], el[2 * u + 1][1]};
-    const int r0 = kTile * t0 + 32 * u + 4 * g + vr, r1 = r0 + 16;
+    constexpr uint32_t kOnes = 0x3F803F80u;       // two bf16 ones
+    l_run = Mfma<uint16_t>::mma(pl, u32x4{kOnes, kOnes, kOnes, kOnes}, l_run);
+    l_run = Mfma<uint16_t>::mma(ph, u32x4{kOnes, kOnes, kOnes, kOnes}, l_run);
 #pragma unroll
-    for (int dt = 0; dt < kHd / 16; ++dt) {
-      const int c = 2 * dt + vc;
-      const uint2 v0 = lds_read_tr16(Vs + 8 * (r0 * 16 + (c ^ (r0 & 15))) + vh);
-      const uint2 v1 = lds_read_tr16(Vs + 8 * (r1 * 16 + (c ^ (r1 & 15))) + vh);
-      const u32x4 vvv{v0.x, v0.y, v1.x, v1.y};
-      o[dt] = Mfma<uint16_t>::mma(pl, vvv, o[dt]);
-      o[dt] = Mfma<uint16_t>::mma(ph, vvv, o[dt]);
+    for (int d0 = 0; d0 < kHd / 16; d0 += 4) {
+      uint32_t a[4];
+      u32x4 v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = va + 8192u * u + 16u * ((2 * (d0 + i) + vc) ^ r0);
+      lds_read_tr16x8(a, v);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[d0 + i] = Mfma<uint16_t>::mma(pl, v[i], o[d0 + i]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[d0 + i] = Mfma<uint16_t>::mma(ph, v[i], o[d0 + i]);
     }
   }
 }
 
 template <int GRP, int NPB>
-__global__ __launch_bounds__(attn_waves(GRP, NPB) * kWave) void k_attn(
+__global__ __launch_bounds__(attn_waves(GRP, NPB) * kWave, attn_occ(GRP, NPB)) void k_attn(
     const uint16_t* __restrict__ qn, const uint16_t* __restrict__ kcache,
     const uint16_t* __restrict__ vcache, const uint16_t* __restrict__ kb,
     const uint16_t* __restrict__ vb, const int32_t* __restrict__ ctx_len, int Cmax, int B,
-    int nh, int nkv, int causal, int ns, int nsub, float* __restrict__ opart,
-    float* __restrict__ mlpart) {
+    int nh, int nkv, int causal, int batch, const int32_t* __restrict__ pre, int W0,
+    float* __restrict__ opart, float* __restrict__ mlpart) {
   using SH = AttnShape<GRP, NPB>;
   constexpr int W = SH::W, NS = SH::NS, KH = SH::KH;
   constexpr int PER = kAttnSlots / 64 / W;       // 1 KB loads per wave per stage
@@ -673,28 +754,39 @@ __global__ __launch_bounds__(attn_waves(GRP, NPB) * kWave) void k_attn(
   constexpr int kMerge = kTile * kHd + 2 * kTile;                // floats per pair
   static_assert(KH == 1 || GRP * NPB * kMerge * 4 <= NS * kAttnSlots * 16, "merge in LDS");
   __shared__ u32x4 lds[NS * kAttnSlots];
-  const int s = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int pair = wave % (GRP * NPB), kh = wave / (GRP * NPB);
   const int hw = pair % GRP, pb = pair / GRP;
   const int t0 = kh * NT;                        // first tile of the wave's keys
   const int g = lane >> 4, li = lane & 15;
+  // this workgroup's share [f, f1) of the sub-chunks, and where it begins:
+  // KV head kvh of sequence b, sub-chunk jc of it
+  const AttnShare share(pre[batch], nkv, W0);
+  const int w = blockIdx.x;
+  int64_t f = share.first(w);
+  const int64_t f1 = share.first(w + 1);
+  if (w >= share.W || f >= f1) return;           // whole workgroup
+  int b = -1;
+  for (int b0 = 0; b0 < batch; b0 += kWave)
+    b += __popcll(__ballot(b0 + lane < batch &&
+                           (int64_t)pre[b0 + lane < batch ? b0 + lane : 0] * nkv <= f));
+  b = __builtin_amdgcn_readfirstlane(b);
+  int nb = pre[b + 1] - pre[b];
+  int kvh, jc;
+  {
+    const uint32_t in = (uint32_t)(f - (int64_t)pre[b] * nkv);   // < nkv nb
+    kvh = (int)(in / (uint32_t)nb);
+    jc = (int)(in - (uint32_t)kvh * (uint32_t)nb);
+  }
+  for (;;) {
+  const int nj = (int)(nb - jc < f1 - f ? nb - jc : f1 - f);   // sub-chunks of this part (>= 1)
   int C = ctx_len[b];
   C = C < 0 ? 0 : (C > Cmax ? Cmax : C);
-  const int nkeys = C + B, kbase = s * kSub * nsub;
-  const size_t pidx = ((((size_t)b * NPB + pb) * nkv + kvh) * ns + s) * GRP + hw;
+  const int nkeys = C + B, kbase = jc * kSub;
+  const size_t pidx = (((size_t)w + (size_t)b * nkv + kvh) * NPB + pb) * GRP + hw;
   float* op = opart + pidx * (kTile * kHd);
   float* ml = mlpart + pidx * (2 * kTile);
-  if (kbase >= nkeys) {                          // whole workgroup: no key in this chunk
-    if (kh == 0 && lane < kTile) {
-      ml[2 * lane] = -INFINITY;
-      ml[2 * lane + 1] = 0.f;
-    }
-    return;
-  }
-  const int left = (nkeys - kbase + kSub - 1) / kSub;
-  const int nj = left < nsub ? left : nsub;      // sub-chunks holding keys (>= 1)
 
   // the wave's q (B operand): query li of block pb, head kvh * GRP + hw
   const int p = pb * kTile + li;
@@ -706,22 +798,22 @@ __global__ __launch_bounds__(attn_waves(GRP, NPB) * kWave) void k_attn(
   for (int ks = 0; ks < kHd / 32; ++ks) qf[ks] = qv ? ld16(qs + 32 * ks) : u32x4{0u, 0u, 0u, 0u};
 
   // Loads of sub-chunks inside the context: the wave's rows (K or V, one
-  // kind per wave) at a per-lane address plus the sub-chunk's first key
-  // times the key stride; other sub-chunks take attn_issue's general path.
+  // kind per wave) at the sub-chunk's first key, a wave-uniform address, plus
+  // a lane offset; other sub-chunks take attn_issue's general path.
   const size_t kst = (size_t)nkv * kHd;           // elements per key row
-  const uint16_t* lp[PER];
-  {
-    const bool isv = wave * PER >= 16;
-    const uint16_t* cb = (isv ? vcache : kcache) + ((size_t)b * Cmax * nkv + kvh) * kHd;
+  const bool isv = wave * PER >= 16;
+  const char* cb =
+      reinterpret_cast<const char*>((isv ? vcache : kcache) + ((size_t)b * Cmax * nkv + kvh) * kHd);
+  uint32_t lp[PER];                               // byte offsets within a sub-chunk
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int row = 4 * ((wave * PER + e) & 15) + (lane >> 4);
-      lp[e] = cb + (size_t)row * kst + 8 * ((lane & 15) ^ (row & 15));
-    }
+  for (int e = 0; e < PER; ++e) {
+    const int row = 4 * ((wave * PER + e) & 15) + (lane >> 4);
+    lp[e] = 2u * (uint32_t)(row * nkv * kHd + 8 * ((lane & 15) ^ (row & 15)));
   }
   __builtin_amdgcn_s_waitcnt(0x0070);            // q landed: from here vmcnt counts the ring
 
-  float m_run = -INFINITY, l_run = 0.f;          // per query li, base-2 units
+  float m_run = -INFINITY;                       // of query li, base-2 units
+  floatx4 l_run{0.f, 0.f, 0.f, 0.f};             // of queries 4 g + i, as O (every column alike)
   floatx4 o[kHd / 16];
 #pragma unroll
   for (int dt = 0; dt < kHd / 16; ++dt) o[dt] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -735,7 +827,7 @@ __global__ __launch_bounds__(attn_waves(GRP, NPB) * kWave) void k_attn(
     u32x4* st_ = lds + slot_ * kAttnSlots;                                                    \
     if (k0_ + kSub <= C) {                                                                    \
       _Pragma("unroll") for (int e_ = 0; e_ < PER; ++e_)                                      \
-        lds_dma16(lp[e_] + (size_t)k0_ * kst, st_ + 64 * (wave * PER + e_));                  \
+        lds_dma16(cb + (size_t)k0_ * kst * 2 + lp[e_], st_ + 64 * (wave * PER + e_));         \
     } else {                                                                                  \
       attn_issue<PER>(st_, wave, lane, k0_, nkeys, C, B, Cmax, nkv, kvh, b, kcache, vcache,   \
                       kb, vb);                                                                \
@@ -744,25 +836,38 @@ __global__ __launch_bounds__(attn_waves(GRP, NPB) * kWave) void k_attn(
 #pragma unroll
   for (int jp = 0; jp < NS - 1; ++jp) XP_ATTN_ISSUE(jp, jp);
   constexpr int kWait = (NS - 2) * PER;          // this wave's loads of the NS - 2 later stages
-  for (int j0 = 0; j0 < nj; j0 += NS) {
-#pragma unroll
-    for (int sl = 0; sl < NS; ++sl) {            // ring slot sl holds sub-chunk j0 + sl
-      const int j = j0 + sl;
-      if (j < nj) {                              // workgroup-uniform
-        // sub-chunk j landed (every wave's loads) and every wave is done
-        // with j - 1, whose slot then takes sub-chunk j + NS - 1
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0x0070 | (kWait & 15) | ((kWait >> 4) << 14));
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        XP_ATTN_ISSUE(j + NS - 1, (sl + NS - 1) % NS);
-        const u32x4* Ks = lds + sl * kAttnSlots;
-        const int kb0 = kbase + j * kSub;
-        attn_step<NT>(Ks, reinterpret_cast<const uint16_t*>(Ks + kAttnSlots / 2), qf, t0, g, li,
-                      qv, kb0 + kSub <= C, kb0, nkeys, C, causal, p, o, m_run, l_run);
+  // The sub-chunks inside the context, then those that reach the block or the
+  // end (masked): loops of their own, 32 keys at a time and the ring slot a
+  // variable, so that one copy of the step with few addresses stays within 128
+  // registers and a second workgroup fits the CU.  With both slots and the mask
+  // in one unrolled body a wave of 64 keys took 166: one workgroup per CU at
+  // 32-position blocks.
+  int jint = (C - kbase) / kSub;
+  jint = jint < 0 ? 0 : (jint < nj ? jint : nj);
+  int slot = 0;
+  auto walk = [&](int j, int jend, auto inside) __attribute__((always_inline)) {
+#pragma unroll 1
+    for (; j < jend; ++j) {
+      // sub-chunk j landed (every wave's loads) and every wave is done with
+      // j - 1, whose slot then takes sub-chunk j + NS - 1
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(0x0070 | (kWait & 15) | ((kWait >> 4) << 14));
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      XP_ATTN_ISSUE(j + NS - 1, slot == 0 ? NS - 1 : slot - 1);
+#pragma unroll 1
+      for (int hf = 0; hf < NT / 2; ++hf) {
+        const int th = t0 + 2 * hf;
+        const u32x4* Ks = lds + slot * kAttnSlots + kTile * 16 * th;
+        attn_step<2, decltype(inside)::value>(
+            Ks, reinterpret_cast<const uint16_t*>(Ks + kAttnSlots / 2), qf, g, li,
+            kbase + j * kSub + kTile * th, nkeys, C, causal, p, o, m_run, l_run);
       }
+      slot = slot + 1 == NS ? 0 : slot + 1;
     }
-  }
+  };
+  walk(0, jint, std::true_type{});
+  walk(jint, nj, std::false_type{});
 #undef XP_ATTN_ISSUE
   __builtin_amdgcn_s_waitcnt(0x0070);            // the clamped loads past the last sub-chunk
   if constexpr (KH == 2) {
@@ -775,22 +880,24 @@ __global__ __launch_bounds__(attn_waves(GRP, NPB) * kWave) void k_attn(
       for (int dt = 0; dt < kHd / 16; ++dt)
 #pragma unroll
         for (int i = 0; i < 4; ++i) mg[(4 * g + i) * kHd + 16 * dt + li] = o[dt][i];
-      if (lane < kTile) {
-        mg[kTile * kHd + lane] = m_run;
-        mg[kTile * kHd + kTile + lane] = l_run;
-      }
+      if (lane < kTile) mg[kTile * kHd + lane] = m_run;
+      if (li == 0) *reinterpret_cast<floatx4*>(mg + kTile * kHd + kTile + 4 * g) = l_run;
     }
     __syncthreads();
-    if (kh == 1) return;                         // whole wave; no barrier follows
-    const float m1 = mg[kTile * kHd + li], l1 = mg[kTile * kHd + kTile + li];
+  }
+  if (KH == 1 || kh == 0) {                      // wave-uniform
+  if constexpr (KH == 2) {
+    const float* mg = reinterpret_cast<const float*>(lds) + pair * kMerge;
+    const float m1 = mg[kTile * kHd + li];
+    const floatx4 l1 = *reinterpret_cast<const floatx4*>(mg + kTile * kHd + kTile + 4 * g);
     const float M = fmaxf(m_run, m1);
     const float Ms = M == -INFINITY ? 0.f : M;
     const float f0 = __builtin_amdgcn_exp2f(m_run - Ms), f1 = __builtin_amdgcn_exp2f(m1 - Ms);
-    l_run = f0 * l_run + f1 * l1;
     m_run = M;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float a0 = __shfl(f0, 4 * g + i, kWave), a1 = __shfl(f1, 4 * g + i, kWave);
+      l_run[i] = a0 * l_run[i] + a1 * l1[i];
 #pragma unroll
       for (int dt = 0; dt < kHd / 16; ++dt)
         o[dt][i] = a0 * o[dt][i] + a1 * mg[(4 * g + i) * kHd + 16 * dt + li];
@@ -800,77 +907,122 @@ __global__ __launch_bounds__(attn_waves(GRP, NPB) * kWave) void k_attn(
   for (int dt = 0; dt < kHd / 16; ++dt)
 #pragma unroll
     for (int i = 0; i < 4; ++i) op[(4 * g + i) * kHd + 16 * dt + li] = o[dt][i];
-  if (lane < kTile) {
-    ml[2 * lane] = m_run;
-    ml[2 * lane + 1] = l_run;
+  if (lane < kTile) ml[2 * lane] = m_run;
+  if (li == 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ml[2 * (4 * g + i) + 1] = l_run[i];
+  }
+  }
+  // on to the next segment of the share
+  f += nj;
+  if (f >= f1) return;                           // whole workgroup
+  jc = 0;
+  if (++kvh == nkv) {
+    kvh = 0;
+    ++b;
+    nb = pre[b + 1] - pre[b];
+  }
+  __syncthreads();                               // every wave is done with the ring's LDS
   }
 }
 
-// One wave per (position m, query head h): merge the chunks in order,
-// attn = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s, to bf16 (m in the
-// base-2 units of k_attn).  Lane j
-// takes the (m, l) of chunk s0 + j; the O rows are then read eight chunks at a
-// time and added in chunk order.  A chunk whose l is 0 (no visible key; its O
-// may be unwritten) contributes nothing.
+// One wave per (position m, HW query heads of one KV head): merge each head's
+// parts in order, attn = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s, to bf16
+// (m in the base-2 units of k_attn).  Lane j takes the (m, l) of part s0 + j; the
+// O rows are then read several parts at a time and added in order, all heads'
+// loads in flight together.  HW is the whole group where the waves are many
+// (one head each, three dependent loads for two outputs a lane, took 56 us at
+// batch 64 x 32), one where they are few and the parts many.  A part whose l is
+// 0 (no visible key) contributes nothing.
+template <int GRP, int HW>
 __global__ __launch_bounds__(256) void k_attn_comb(const float* __restrict__ opart,
                                                    const float* __restrict__ mlpart, int M, int B,
-                                                   int npb, int nh, int nkv, int grp, int ns,
+                                                   int npb, int nkv, int batch,
+                                                   const int32_t* __restrict__ pre, int W0,
                                                    uint16_t* __restrict__ attn) {
   const int lane = threadIdx.x & 63;
-  const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (w >= M * nh) return;                       // whole wave
-  const int m = w / nh, h = w - m * nh;
+  const int wv = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  constexpr int NH = GRP / HW;                   // waves of a KV head
+  if (wv >= M * nkv * NH) return;                // whole wave
+  const int m = wv / (nkv * NH), kh = wv - m * (nkv * NH), kvh = kh / NH, h0 = HW * (kh % NH);
   const int b = m / B, p = m - b * B, pb = p / kTile, q = p - pb * kTile;
-  const int kvh = h / grp, wv = h - kvh * grp, z = b * npb + pb;
-  const size_t base = (((size_t)z * nkv + kvh) * ns) * grp + wv;
-  auto mlv = [&](int s, float& ms, float& ls) {
-    if (s < ns) {
-      const size_t pi = base + (size_t)s * grp;
-      ms = mlpart[pi * 2 * kTile + 2 * q];
-      ls = mlpart[pi * 2 * kTile + 2 * q + 1];
-    } else {
-      ms = -INFINITY;
-      ls = 0.f;
-    }
+  // the segment's parts: shares wa .. wa + ns - 1, partial numbers share + segment
+  const AttnShare share(pre[batch], nkv, W0);
+  const int nb = pre[b + 1] - pre[b];
+  const int64_t fa = (int64_t)pre[b] * nkv + (int64_t)kvh * nb;
+  const int wa = share.of(fa), ns = share.of(fa + nb - 1) - wa + 1;
+  const size_t first = (((size_t)wa + (size_t)b * nkv + kvh) * npb + pb) * GRP + h0;
+  const size_t step = (size_t)npb * GRP;
+  auto mlv = [&](int s, int h, float& ms, float& ls) {
+    const size_t pi = first + (size_t)(s < ns ? s : ns - 1) * step + h;
+    ms = mlpart[pi * 2 * kTile + 2 * q];
+    ls = s < ns ? mlpart[pi * 2 * kTile + 2 * q + 1] : 0.f;
   };
-  float mm = -INFINITY;
-  for (int s0 = 0; s0 < ns; s0 += kWave) {
-    float ms, ls;
-    mlv(s0 + lane, ms, ls);
-    if (ls > 0.f) mm = fmaxf(mm, ms);
+  float mm[HW], Ll[HW], o0[HW], o1[HW];
+#pragma unroll
+  for (int h = 0; h < HW; ++h) {
+    mm[h] = -INFINITY;
+    Ll[h] = o0[h] = o1[h] = 0.f;
   }
-#pragma unroll
-  for (int k = 32; k >= 1; k >>= 1) mm = fmaxf(mm, __shfl_xor(mm, k, kWave));
-  float Ll = 0.f, o0 = 0.f, o1 = 0.f;
   for (int s0 = 0; s0 < ns; s0 += kWave) {
-    float ms, ls;
-    mlv(s0 + lane, ms, ls);
-    const float f = ls > 0.f ? __builtin_amdgcn_exp2f(ms - mm) : 0.f;
-    Ll += f * ls;
-    const int cnt = ns - s0 < kWave ? ns - s0 : kWave;
-    for (int j0 = 0; j0 < cnt; j0 += 8) {
-      float fj[8], v0[8], v1[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int j = j0 + u < cnt ? j0 + u : cnt - 1;
-        fj[u] = __shfl(f, j, kWave);
-        if (j0 + u >= cnt) fj[u] = 0.f;
-        const size_t pi = base + (size_t)(s0 + j) * grp;
-        v0[u] = opart[pi * (kTile * kHd) + q * kHd + lane];
-        v1[u] = opart[pi * (kTile * kHd) + q * kHd + lane + 64];
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        o0 += fj[u] != 0.f ? fj[u] * v0[u] : 0.f;
-        o1 += fj[u] != 0.f ? fj[u] * v1[u] : 0.f;
-      }
+    for (int h = 0; h < HW; ++h) {
+      float ms, ls;
+      mlv(s0 + lane, h, ms, ls);
+      if (ls > 0.f) mm[h] = fmaxf(mm[h], ms);
     }
   }
-  const float L = wave_sum(Ll);
-  const float inv = L > 0.f ? 1.f / L : 0.f;     // L > 0: every query sees its own key
-  uint16_t* dst = attn + (size_t)m * nh * kHd + (size_t)h * kHd;
-  dst[lane] = f32_to_bf16_rne(o0 * inv);
-  dst[lane + 64] = f32_to_bf16_rne(o1 * inv);
+#pragma unroll
+  for (int h = 0; h < HW; ++h)
+#pragma unroll
+    for (int k = 32; k >= 1; k >>= 1) mm[h] = fmaxf(mm[h], __shfl_xor(mm[h], k, kWave));
+  for (int s0 = 0; s0 < ns; s0 += kWave) {
+    float f[HW];
+#pragma unroll
+    for (int h = 0; h < HW; ++h) {
+      float ms, ls;
+      mlv(s0 + lane, h, ms, ls);
+      f[h] = ls > 0.f ? __builtin_amdgcn_exp2f(ms - mm[h]) : 0.f;
+      Ll[h] += f[h] * ls;
+    }
+    const int cnt = ns - s0 < kWave ? ns - s0 : kWave;
+    constexpr int kU = HW >= 8 ? 4 : 8;
+    auto add = [&](int j0, auto un) {             // parts j0 .. j0 + U - 1
+      constexpr int U = un;
+      float v0[U][HW], v1[U][HW];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = j0 + u < cnt ? j0 + u : cnt - 1;
+        const size_t pi = first + (size_t)(s0 + j) * step;
+#pragma unroll
+        for (int h = 0; h < HW; ++h) {
+          const float* src = opart + (pi + h) * (kTile * kHd) + q * kHd + lane;
+          v0[u][h] = src[0];
+          v1[u][h] = src[64];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int h = 0; h < HW; ++h) {
+          const float fj = j0 + u < cnt ? __shfl(f[h], j0 + u < cnt ? j0 + u : 0, kWave) : 0.f;
+          o0[h] += fj != 0.f ? fj * v0[u][h] : 0.f;
+          o1[h] += fj != 0.f ? fj * v1[u][h] : 0.f;
+        }
+    };
+    if (cnt <= 2)                                 // the common case of long contexts
+      add(0, std::integral_constant<int, 2>{});
+    else
+      for (int j0 = 0; j0 < cnt; j0 += kU) add(j0, std::integral_constant<int, kU>{});
+  }
+#pragma unroll
+  for (int h = 0; h < HW; ++h) {
+    const float L = wave_sum(Ll[h]);
+    const float inv = L > 0.f ? 1.f / L : 0.f;   // L > 0: every query sees its own key
+    uint16_t* dst = attn + (((size_t)m * nkv + kvh) * GRP + h0 + h) * kHd;
+    dst[lane] = f32_to_bf16_rne(o0[h] * inv);
+    dst[lane + 64] = f32_to_bf16_rne(o1[h] * inv);
+  }
 }
 
 // silu(gate) * up to bf16, gate and up side by side in one row of 2 F
@@ -1052,24 +1204,21 @@ static size_t carve(const xp_layer& L, size_t Mx, size_t nparts, size_t gu_rows,
   return off;
 }
 
-// Attention chunking of one call: chunks of nsub 64-key sub-chunks, about
-// kAttnWgs workgroups (sequence, KV head, chunk) in all (one sub-chunk each
-// at small calls), so that the partials stay few.  Returns the partial count
-// batch * npb * nkv * ns * grp.
+// Attention shares of one call: W workgroups (at most one per 64-key sub-chunk
+// that the call could have), and the partials they write at most: (W + batch
+// nkv - 1) npb grp.
 struct AttnPlan {
-  int nsub, ns;
+  int W;
   size_t parts;
 };
-static AttnPlan attn_plan(const xp_layer& L, int batch, int B, int C_max, int nsub) {
-  const int npb = (B + kTile - 1) / kTile;
-  const int ns = attn_chunks(C_max, B, kSub * nsub);
-  return {nsub, ns, (size_t)batch * npb * L.nkv * ns * L.grp};
+static AttnPlan attn_plan(const xp_layer& L, int batch, int B, int W) {
+  const size_t npb = (B + kTile - 1) / kTile;
+  return {W, ((size_t)W + (size_t)batch * L.nkv - 1) * npb * L.grp};
 }
 static AttnPlan attn_plan_default(const xp_layer& L, int batch, int B, int C_max) {
   const size_t w64 = (size_t)batch * L.nkv * attn_chunks(C_max, B, kSub);
-  int nsub = (int)(w64 / kAttnWgs);
-  nsub = nsub < 1 ? 1 : (nsub > 256 ? 256 : nsub);
-  return attn_plan(L, batch, B, C_max, nsub);
+  const int wgs = kAttnWgs / 2 * attn_cu_wgs(L.grp, (B + kTile - 1) / kTile);
+  return attn_plan(L, batch, B, (int)std::min(w64, (size_t)wgs));
 }
 
 extern "C" xp_status xp_layer_create(const xp_layer_weights* w, int32_t max_batch, int32_t max_B,
@@ -1095,13 +1244,9 @@ extern "C" xp_status xp_layer_create(const xp_layer_weights* w, int32_t max_batc
   L->max_B = max_B;
   L->max_ctx = max_ctx;
   const size_t Mx = (size_t)max_batch * max_B;
-  // attention partials: a call has at most max(2 kAttnWgs, w64 / 256) + one
-  // per (sequence, KV head) chunks, w64 its (sequence, KV head, 64-key
-  // sub-chunk) triples, and npb grp partials per chunk
+  // attention partials (attn_plan): any call has at most these
   const size_t qmax = (size_t)max_batch * L->nkv, npbmax = (max_B + kTile - 1) / kTile;
-  const size_t w64max = qmax * (size_t)attn_chunks(max_ctx, max_B, kSub);
-  const size_t nparts =
-      (std::max((size_t)2 * kAttnWgs, (w64max + 255) / 256) + qmax) * npbmax * L->grp;
+  const size_t nparts = (kAttnWgs + qmax) * npbmax * L->grp;
   const size_t gu = gu_rows_for(*L, Mx), pf = part_floats_for(Mx);
   const size_t total = carve(*L, Mx, nparts, gu, pf, nullptr, nullptr);
   const hipError_t e = hipMalloc(&L->ws, total);
@@ -1176,22 +1321,26 @@ static hipError_t linear(const LayerBufs& b, const uint16_t* W0, const uint16_t*
   const int nb = (M + kTile - 1) / kTile;
   const int P = nb >= 4 ? 4 : (nb >= 2 ? 2 : 1);
   // two row tiles per workgroup (stacked row counts are multiples of 32) once
-  // several position blocks reuse each X fragment; one at a single block,
-  // where the workgroup count matters more
-  const int mode = glu ? 1 : (P > 1 ? 2 : 0);
+  // several position blocks reuse each X fragment and the workgroups still
+  // cover the CUs (H = 2048 at 32 positions: 88 -> 81 us a forward); else one
+  const bool two = P > 1 && N / (2 * kTile) >= 256;
+  const int mode = glu ? 1 : (two ? 2 : 0);
   const dim3 grid(N / (mode == 2 ? 2 * kTile : kTile), (M + kTile * P - 1) / (kTile * P)),
       block(kLinWaves * kWave);
 #define XP_LIN(PP, MM)                                                                        \
   hipLaunchKernelGGL((k_linear<PP, MM>), grid, block, 0, st, W0, W1, W2, n0, n1, K, X, M, R, \
                      ldr, Y, Yb, ldy)
-  if (glu) {
+  if (mode == 1) {
     if (P == 4) XP_LIN(4, 1);
     else if (P == 2) XP_LIN(2, 1);
     else XP_LIN(1, 1);
+  } else if (mode == 0) {
+    if (P == 4) XP_LIN(4, 0);
+    else if (P == 2) XP_LIN(2, 0);
+    else XP_LIN(1, 0);
   } else {
     if (P == 4) XP_LIN(4, 2);
-    else if (P == 2) XP_LIN(2, 2);
-    else XP_LIN(1, 0);
+    else XP_LIN(2, 2);
   }
 #undef XP_LIN
   return hipGetLastError();
@@ -1227,7 +1376,9 @@ static xp_status forward(const xp_layer& L, const LayerBufs& b, const AttnPlan& 
   const int M = batch * B, H = L.H, nh = L.nh, nkv = L.nkv, F = L.ffn, grp = L.grp;
   const int nhd = nh * kHd, kvd = nkv * kHd, ldq = nhd + 2 * kvd;
   const int npb = (B + kTile - 1) / kTile;
-  const int ns = ap.ns, nsub = ap.nsub;
+  // the work list of the attention lies in x1, which nothing holds before the
+  // output projection
+  int32_t* pre = reinterpret_cast<int32_t*>(b.x1);
   if (ap.parts > b.nparts)
     return layer_fail(Lerr, XP_EINVAL, "attention partials exceed the buffers");   // not reached
   float* hout = h_f32 ? h_f32 : b.h32;
@@ -1251,15 +1402,17 @@ static xp_status forward(const xp_layer& L, const LayerBufs& b, const AttnPlan& 
   int sq = 1, so = 1, sd = 1;                    // k splits of q/k/v, output, down
   XP_LINEAR("q/k/v", b, L.Wq, L.Wk, L.Wv, nhd, kvd, ldq, H, b.u, M, nullptr, 0, b.qkv, nullptr,
             ldq, false, &sq, st);
+  // about two workgroups per CU, each wave at least one head slot
+  const int qy = std::max(1, std::min((nh + 2 * nkv) / 4, 512 / M));
   XP_STEP("qk-norm/rope",
-          hipLaunchKernelGGL(k_qkrope, dim3(M), dim3(256), 0, st, sq > 1 ? b.part : b.qkv, sq,
+          hipLaunchKernelGGL(k_qkrope, dim3(M, qy), dim3(256), 0, st, sq > 1 ? b.part : b.qkv, sq,
                              (size_t)M * ldq, ldq, B, nh, nkv, ctx_len, C_max, L.g_q, L.g_k,
-                             L.eps, L.theta, b.qn, b.kb, b.vb));
+                             L.eps, std::log2((double)L.theta), b.qn, b.kb, b.vb, batch, pre));
 #define XP_ATTN(GG, PB)                                                                      \
-  hipLaunchKernelGGL((k_attn<GG, PB>), dim3(ns, nkv, batch),                                  \
+  hipLaunchKernelGGL((k_attn<GG, PB>), dim3(ap.W),                                            \
                      dim3(attn_waves(GG, PB) * kWave), 0, st,                                 \
                      b.qn, (const uint16_t*)k_cache, (const uint16_t*)v_cache, b.kb, b.vb,    \
-                     ctx_len, C_max, B, nh, nkv, causal, ns, nsub, b.opart, b.mlpart)
+                     ctx_len, C_max, B, nh, nkv, causal, batch, pre, ap.W, b.opart, b.mlpart)
   if (npb == 1) {
     if (grp == 1) XP_STEP("attention", XP_ATTN(1, 1));
     else if (grp == 2) XP_STEP("attention", XP_ATTN(2, 1));
@@ -1272,10 +1425,21 @@ static xp_status forward(const xp_layer& L, const LayerBufs& b, const AttnPlan& 
     else XP_STEP("attention", XP_ATTN(8, 2));
   }
 #undef XP_ATTN
-  const int cw = M * nh;
-  XP_STEP("attention combine",
-          hipLaunchKernelGGL(k_attn_comb, dim3((cw + 3) / 4), dim3(256), 0, st, b.opart,
-                             b.mlpart, M, B, npb, nh, nkv, grp, ns, b.attn));
+  // whole groups from 1024 waves on
+#define XP_COMB1(GG, HH)                                                                     \
+  hipLaunchKernelGGL((k_attn_comb<GG, HH>), dim3((M * nkv * (GG / HH) + 3) / 4), dim3(256), 0, \
+                     st, b.opart, b.mlpart, M, B, npb, nkv, batch, pre, ap.W, b.attn)
+#define XP_COMB(GG)                                                                          \
+  do {                                                                                       \
+    if (M * nkv >= 1024) XP_STEP("attention combine", XP_COMB1(GG, GG));                      \
+    else XP_STEP("attention combine", XP_COMB1(GG, 1));                                       \
+  } while (0)
+  if (grp == 1) XP_STEP("attention combine", XP_COMB1(1, 1));
+  else if (grp == 2) XP_COMB(2);
+  else if (grp == 4) XP_COMB(4);
+  else XP_COMB(8);
+#undef XP_COMB1
+#undef XP_COMB
   XP_LINEAR("output", b, L.Wo, nullptr, nullptr, H, 0, H, nhd, b.attn, M, b.x32, H, b.x1,
             nullptr, H, false, &so, st);
   // x1 = Wo attn + x: written by the projection, or here from its slabs
@@ -1367,8 +1531,8 @@ extern "C" xp_status xp_layer_forward_noalloc(const xp_layer_weights* w, int32_t
   const size_t M = (size_t)batch * B;
   if (!rows_fit_int32(L, (int64_t)M))
     return layer_fail(nullptr, XP_EINVAL, "batch*B*max(H, heads*128, ffn) reaches 2^31");
-  // The buffers the call needs, its partials at the default chunking; if
-  // those do not fit, chunks of more 64-key sub-chunks (fewer partials).
+  // The buffers the call needs, its partials at the default number of shares;
+  // if those do not fit, fewer and longer shares.
   const size_t gu = gu_rows_for(L, M);
   const size_t fixed = carve(L, M, 0, gu, 0, nullptr, nullptr);
   const size_t per_part = (size_t)kTile * kHd * 4 + (size_t)2 * kTile * 4;   // opart + mlpart
@@ -1378,19 +1542,14 @@ extern "C" xp_status xp_layer_forward_noalloc(const xp_layer_weights* w, int32_t
                       M, fixed + per_part, kScratchBytes);
   const size_t max_parts = (kScratchBytes - fixed - 2 * 256) / per_part;
   AttnPlan ap = attn_plan_default(L, batch, B, C_max);
-  if (ap.parts > max_parts) {
-    const int chunks64 = attn_chunks(C_max, B, kSub);
-    int lo = ap.nsub, hi = chunks64;             // ap at nsub = chunks64 has ns = 1
-    if (attn_plan(L, batch, B, C_max, hi).parts > max_parts)
+  if (ap.parts > max_parts) {                    // as many shares as the partials allow
+    const size_t fit = max_parts / (((size_t)B + kTile - 1) / kTile * L.grp);   // W + segments - 1
+    const size_t segs = (size_t)batch * L.nkv;
+    if (fit < segs)
       return layer_fail(nullptr, XP_EINVAL,
                         "%d sequences x %d KV heads need more attention partials than the static "
                         "scratch holds beside %zu positions", batch, L.nkv, M);
-    while (lo + 1 < hi) {                        // smallest nsub whose partials fit
-      const int mid = lo + (hi - lo) / 2;
-      if (attn_plan(L, batch, B, C_max, mid).parts > max_parts) lo = mid;
-      else hi = mid;
-    }
-    ap = attn_plan(L, batch, B, C_max, hi);
+    ap = attn_plan(L, batch, B, (int)(fit - segs + 1));
   }
   char* base = nullptr;
   const hipError_t e = scratch_ptr(&base);

@@ -1,0 +1,81 @@
+"""The attention's shares of the context against the fp64 oracle (needs an
+MI355X): calls whose work list is shorter than the workgroups, one sequence cut
+into many parts, many short sequences in one share, shares that end inside the
+block's own keys, every group size and both block widths, and the static-scratch
+forward at its limit of partials."""
+import numpy as np
+import pytest
+
+import oracle as O
+import synth
+from paper_2608_02438_amd.xpress import LAYER_WEIGHT_NAMES
+
+pytestmark = pytest.mark.gpu
+
+
+# (KV heads, group, B, contexts): sub-chunks of 64 keys counted per KV head
+CASES = [
+    (1, 1, 1, [0]),                                   # one sub-chunk in all
+    (2, 4, 16, [63, 64, 65, 127]),                    # ends around a sub-chunk's
+    (1, 2, 32, [40000]),                              # one segment over every share
+    (2, 8, 7, [9000, 0, 1, 5000]),                    # long and empty ones side by side
+    (4, 4, 32, [0, 1, 31, 32, 33, 100] * 12),         # several segments in a share
+    (8, 1, 16, [300] * 65),                           # more sequences than a wave's lanes
+    (2, 8, 32, [2000, 17, 4097]),                     # sixteen waves
+]
+
+
+@pytest.mark.parametrize("nkv,grp,B,ctx", CASES)
+@pytest.mark.parametrize("causal", [True, False])
+def test_attention_shares(nkv, grp, B, ctx, causal):
+    import torch
+    from paper_2608_02438_amd.xpress import Layer, device_tensor
+    print(f"shares: nkv={nkv} grp={grp} B={B} sequences={len(ctx)} max ctx={max(ctx)} "
+          f"causal={causal}", flush=True)
+    nh = nkv * grp
+    if nh * 128 % 256:                                # n_heads * 128: a multiple of 256
+        nkv, nh = 2 * nkv, 2 * nh
+    batch, cmax = len(ctx), max(max(ctx), 1)
+    w = synth.scaled(synth.configs.QWEN_B1, index=970 + nkv + grp, H=256, B=B, batch=batch,
+                     n_heads=nh, n_kv_heads=nkv, ffn=256, ctx_len=None, ctx_len_range=None)
+    weights = synth.make_layer_weights(w)
+    inp = synth.make_layer_inputs(w, c_max=cmax)
+    inp.ctx_len = np.array(ctx, dtype=np.int32)
+    dw = {k: device_tensor(weights[k]) for k in LAYER_WEIGHT_NAMES}
+    layer = Layer(dw, w.H, nh, nkv, w.ffn, max_batch=batch, max_B=B, max_ctx=cmax)
+    args = [device_tensor(a) for a in (inp.x, inp.k_cache, inp.v_cache, inp.ctx_len)]
+    h, _ = layer.forward(*args, causal=causal)
+    again, _ = layer.forward(*args, causal=causal)
+    h, again = h.cpu().numpy(), again.cpu().numpy()
+    layer.close()
+    assert np.array_equal(h.view(np.uint32), again.view(np.uint32))
+    some = sorted({0, 1, 2, 3, batch - 1} & set(range(batch)))
+    LP = O.layer_ref.LayerParams.from_arrays(weights, nh, nkv, 128)
+    ref = O.layer_ref.layer_forward(LP, inp.x[some], inp.k_cache[some], inp.v_cache[some],
+                                    inp.ctx_len[some], causal=causal)
+    # the layer parity tests' bar: one bf16 unit at the output's scale
+    assert np.abs(h[some] - ref).max() <= max(2e-2, 2.0 ** -8 * np.abs(ref).max())
+
+
+def test_static_scratch_with_fewer_shares():
+    """65 positions: the partials of the default shares do not fit beside the
+    buffers of the Qwen3-8B shape at this many KV heads, so fewer shares serve."""
+    import torch
+    from paper_2608_02438_amd.xpress import device_tensor, layer_forward_noalloc, \
+        layer_weights_struct
+    w = synth.scaled(synth.configs.QWEN_B1, index=990, H=256, B=32, batch=8, n_heads=32,
+                     n_kv_heads=4, ffn=256, ctx_len=None, ctx_len_range=None)
+    print("static scratch, 8 x 32 positions, 32 heads", flush=True)
+    weights = synth.make_layer_weights(w)
+    inp = synth.make_layer_inputs(w, c_max=3000)
+    inp.ctx_len = np.array([3000, 0, 64, 2999, 1, 700, 128, 1500], dtype=np.int32)
+    dw = {k: device_tensor(weights[k]) for k in LAYER_WEIGHT_NAMES}
+    st = layer_weights_struct(dw, w.H, 32, 4, w.ffn)
+    h32 = torch.empty((8, 32, 256), dtype=torch.float32, device="cuda")
+    hb = torch.empty((8, 32, 256), dtype=torch.bfloat16, device="cuda")
+    layer_forward_noalloc(st, *[device_tensor(a) for a in (inp.x, inp.k_cache, inp.v_cache,
+                                                           inp.ctx_len)], h32, hb)
+    LP = O.layer_ref.LayerParams.from_arrays(weights, 32, 4, 128)
+    ref = O.layer_ref.layer_forward(LP, inp.x, inp.k_cache, inp.v_cache, inp.ctx_len)
+    got = h32.cpu().numpy()
+    assert np.abs(got - ref).max() <= max(2e-2, 2.0 ** -8 * np.abs(ref).max())
