@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kGWaves * kWave) void k_lmhead_gemm(
   // positions;
   // on 256 x 256 tiles (matrix-bound, and the h tile shared through L2 by
   // the row tiles of one position tile) it cost 1-3%
-  const int kshift = BN == 128 ? ((sc.k8q & 7) * (H / kGK)) >> 3 : 0;
+  const int kshift = BN == 128 ? ((sc.k8q & 7) * (H / GemmShape<BN, BM>::GK)) >> 3 : 0;
   gemm_tiles<BN, BM>(rows, epi, X, H, M, H, ntl, p0, lds, kshift);
 }
 
@@ -192,7 +192,7 @@ int gemm_units(const xp_handle* h, int M) {
 int gemm_units_max(const xp_handle* h) { return gemm_units(h, 1); }
 
 bool lmhead_gemm_ok(const xp_handle* h, int M) {
-  return h->dtype == XP_BF16 && M > kTile && h->H % kGK == 0;
+  return h->dtype == XP_BF16 && M > kTile && h->H % 64 == 0;
 }
 
 hipError_t launch_lmhead_gemm(xp_handle* h, int M, const void* hidden, const uint8_t* temp,

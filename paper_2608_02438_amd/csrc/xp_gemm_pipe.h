@@ -6,9 +6,10 @@
 //
 // A tile is BN weight rows x BM positions, computed by 8 waves: wave w owns
 // rows (w & 1) BN/2 .. + BN/2 and positions (w >> 1) BM/4 .. + BM/4 as
-// 32 x 32 blocks.  k advances 32 per stage through an LDS ring of NS stages
-// filled by global_load_lds_dwordx4 (no staging registers).  Only waves 0-3,
-// one per SIMD (a workgroup's wave w runs on SIMD w mod 4), issue the loads:
+// 32 x 32 blocks.  k advances GK per stage (64 on 128 x 128 tiles, 32 on 256 x
+// 256) through an LDS ring of NS stages filled by global_load_lds_dwordx4 (no
+// staging registers).  Only waves 0-3, one per SIMD (a workgroup's wave w runs on
+// SIMD w mod 4), issue the loads:
 // wave w < 4 fills W slots [64 WI w, 64 WI (w + 1)) and X slots
 // [64 HI w, 64 HI (w + 1)) with 1 KB instructions (WI, HI for the 4 loading
 // waves).  A load instruction can wait many cycles at issue while the
@@ -20,13 +21,18 @@
 // positions, no change at 2048; waves 4-7 as the loading waves, or the loads
 // split over both halves of a stage, were slower.
 //
-// A stage row holds 32 k (four 16-byte chunks); chunk c of row r sits in
-// slot 4 r + (c ^ swz(r)), swz(r) = (r / 4) mod 4: four consecutive
-// rows fill one 256-byte line of the 64 banks and the next three groups of
-// four rotate their chunks, so an operand read (32 rows, one chunk) meets no
-// bank conflict (SQ_LDS_BANK_CONFLICT reads zero; with swz(r) = ((r / 2) xor
-// (r / 8)) mod 4 it counted conflicts on a fifth of the CU cycles and the
-// GEMM ran 7-14% slower).  The ring runs on across tile boundaries, so the
+// GK is 64 where the launch is bound by HBM: a load instruction then covers 8
+// whole 128-byte lines of rows 8 KB apart instead of 16 half lines whose other
+// halves follow a stage later (LM head at 32 / 65 / 128 positions: 295 / 294 /
+// 312 -> 284 / 269 / 290 us; on 256 x 256 tiles, bound by the matrix pipeline, a
+// walk of whole lines made no difference, and 64 k leave two stages of LDS).
+// A stage row holds GK k (four or eight 16-byte chunks); chunk c of row r sits
+// in slot 4 r + (c ^ ((r / 4) mod 4)) or 8 r + (c ^ ((r / 2) mod 8)): the rows
+// that share a 256-byte line of the 64 banks and the next groups of them rotate
+// their chunks, so an operand read (32 rows, one chunk) meets no bank conflict
+// (SQ_LDS_BANK_CONFLICT reads zero at 4 chunks; with ((r / 2) xor (r / 8)) mod 4
+// it counted conflicts on a fifth of the CU cycles and the GEMM ran 7-14%
+// slower).  The ring runs on across tile boundaries, so the
 // next tile's first stages load while the previous tile's epilogue runs.
 //
 // Layout of the 32x32x16 operation (checked on gfx950): lane l holds row
@@ -51,20 +57,24 @@ __device__ __forceinline__ floatx16 mma32(u32x4 a, u32x4 b, floatx16 c) {
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-__device__ __forceinline__ int gswz(int r) { return (r >> 2) & 3; }
-__device__ __forceinline__ int gslot(int r, int c) { return 4 * r + (c ^ gswz(r)); }
-
 template <int BN, int BM>
 struct GemmShape {
+  static constexpr int GK = BN == 128 ? 64 : kGK;                      // k per stage
+  static constexpr int CH = GK / 8;                                    // 16-byte chunks of a stage row
   static constexpr int RW = BN / 2, PW = BM / 4;                       // rows, positions per wave
   static constexpr int NA = RW / 32, NB = PW / 32;                     // 32 x 32 blocks per wave
-  static constexpr int WS = BN * kGK * 2 / 16, HS = BM * kGK * 2 / 16; // slots per operand stage
+  static constexpr int WS = BN * CH, HS = BM * CH;                     // slots per operand stage
   static constexpr int WI = WS / 64 / kGLoaders, HI = HS / 64 / kGLoaders; // 1 KB loads per loading wave
   static constexpr int NS0 = 163840 / ((WS + HS) * 16);
   static constexpr int NS = NS0 < 8 ? NS0 : 8;                         // ring stages
   static constexpr int SLOTS = NS * (WS + HS);
   static_assert(WI >= 1 && HI >= 1 && NA >= 1 && NB >= 1, "tile shape");
   static_assert(SLOTS * 16 <= 163840, "LDS");
+  // the chunk that row r's chunk c is stored at (its own inverse)
+  __device__ static __forceinline__ int swz(int r, int c) {
+    return c ^ (CH == 8 ? (r >> 1) & 7 : (r >> 2) & 3);
+  }
+  __device__ static __forceinline__ int slot(int r, int c) { return CH * r + swz(r, c); }
 };
 
 // Where a wave sits in the tile, for the epilogues.
@@ -80,7 +90,7 @@ struct GemmLane {
 // local row r (0 <= r < BN) at that k.  epi(ti, acc, where) consumes tile
 // ti's accumulators; the pipeline clears them afterwards.  lds holds
 // GemmShape<BN, BM>::SLOTS 16-byte slots.  Every tile walks its k chunks
-// starting at chunk kshift (0 <= kshift < K / 32) and wrapping around.
+// starting at chunk kshift (0 <= kshift < K / GK) and wrapping around.
 template <int BN, int BM, class Rows, class Epi>
 __device__ __forceinline__ void gemm_tiles(Rows& rows, Epi& epi, const uint16_t* __restrict__ X,
                                            int ldx, int M, int K, int ntl, int p0, u32x4* lds,
@@ -88,7 +98,9 @@ __device__ __forceinline__ void gemm_tiles(Rows& rows, Epi& epi, const uint16_t*
   using G = GemmShape<BN, BM>;
   constexpr int RW = G::RW, PW = G::PW, NA = G::NA, NB = G::NB, WS = G::WS, HS = G::HS;
   constexpr int WI = G::WI, HI = G::HI, NS = G::NS;
-  const int nk = K / kGK;
+  constexpr int GK = G::GK, CH = G::CH, KS = GK / 16;                  // KS k steps per stage
+  static_assert(KS % 2 == 0, "fragment sets alternate");
+  const int nk = K / GK;
   const int nstages = ntl * nk;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -101,16 +113,16 @@ __device__ __forceinline__ void gemm_tiles(Rows& rows, Epi& epi, const uint16_t*
   int wrow[WI], wcol[WI], hrow[HI];
 #pragma unroll
   for (int j = 0; j < WI; ++j) {
-    const int row = (64 * (WI * li + j) + lane) >> 2;
+    const int row = (64 * (WI * li + j) + lane) / CH;
     wrow[j] = row;
-    wcol[j] = 8 * ((lane & 3) ^ gswz(row));
+    wcol[j] = 8 * G::swz(row, lane % CH);
   }
 #pragma unroll
   for (int j = 0; j < HI; ++j) {
-    const int row = (64 * (HI * li + j) + lane) >> 2;
+    const int row = (64 * (HI * li + j) + lane) / CH;
     int hr = p0 + row;
     hr = hr < M ? hr : M - 1;
-    hrow[j] = hr * ldx + 8 * ((lane & 3) ^ gswz(row));
+    hrow[j] = hr * ldx + 8 * G::swz(row, lane % CH);
   }
   int iss_tile = -1;                                               // tile whose rows are cached
   auto prep = [&](int gs) {
@@ -127,10 +139,10 @@ __device__ __forceinline__ void gemm_tiles(Rows& rows, Epi& epi, const uint16_t*
     const int st = gs % NS;
 #pragma unroll
     for (int j = 0; j < WI; ++j)
-      lds_dma16(rows.row(wrow[j]) + kc * kGK + wcol[j], &lds[st * (WS + HS) + 64 * (WI * li + j)]);
+      lds_dma16(rows.row(wrow[j]) + kc * GK + wcol[j], &lds[st * (WS + HS) + 64 * (WI * li + j)]);
 #pragma unroll
     for (int j = 0; j < HI; ++j)
-      lds_dma16(X + (size_t)(unsigned)hrow[j] + rows.xk + kc * kGK,
+      lds_dma16(X + (size_t)(unsigned)hrow[j] + rows.xk + kc * GK,
                 &lds[st * (WS + HS) + WS + 64 * (HI * li + j)]);
   };
 
@@ -147,10 +159,10 @@ __device__ __forceinline__ void gemm_tiles(Rows& rows, Epi& epi, const uint16_t*
     const int base = (gs % NS) * (WS + HS);
     const int c = 2 * ks + where.lk;
 #pragma unroll
-    for (int a = 0; a < NA; ++a) av[a] = lds[base + gslot(where.wv * RW + a * 32 + where.lr, c)];
+    for (int a = 0; a < NA; ++a) av[a] = lds[base + G::slot(where.wv * RW + a * 32 + where.lr, c)];
 #pragma unroll
     for (int cc = 0; cc < NB; ++cc)
-      bv[cc] = lds[base + WS + gslot(where.wp * PW + cc * 32 + where.lr, c)];
+      bv[cc] = lds[base + WS + G::slot(where.wp * PW + cc * 32 + where.lr, c)];
   };
   auto mm = [&](const u32x4 (&av)[NA], const u32x4 (&bv)[NB]) {
 #pragma unroll
@@ -183,8 +195,8 @@ __device__ __forceinline__ void gemm_tiles(Rows& rows, Epi& epi, const uint16_t*
   __builtin_amdgcn_s_waitcnt(0xc07f);
   int ti = 0, kc = 0;
   for (int gs = 0; gs < nstages; ++gs) {
-    // k step 1 of stage gs is read while k step 0 multiplies; the barrier
-    // between the two k steps (wait: stage gs + 1 landed for this wave, and
+    // each k step's fragments are read while the one before multiplies; the
+    // barrier before the last k step (wait: stage gs + 1 landed for this wave, and
     // this wave's reads of stage gs are done) makes stage gs + 1 readable for
     // everyone and frees the slot of stage gs for stage gs + NS.  Other
     // vector-memory operations (the epilogue's stores) only make the wait
@@ -193,15 +205,18 @@ __device__ __forceinline__ void gemm_tiles(Rows& rows, Epi& epi, const uint16_t*
     // scheduling groups below), so the LDS reads overlap the matrix pipe; the
     // row bookkeeping of stage gs + NS runs before the wait and its loads are
     // issued after the barrier, behind the second half's matrix operations.
-    rd(gs, 1, fa[1], fb[1]);
-    mm(fa[0], fb[0]);
 #pragma unroll
-    for (int q = 0; q < NA + NB; ++q) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    for (int ks = 0; ks + 1 < KS; ++ks) {
+      rd(gs, ks + 1, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
+      mm(fa[ks & 1], fb[ks & 1]);
+#pragma unroll
+      for (int q = 0; q < NA + NB; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);
-    __builtin_amdgcn_sched_barrier(0);
     prep(gs + NS);
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");

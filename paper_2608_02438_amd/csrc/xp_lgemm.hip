@@ -163,15 +163,17 @@ __global__ __launch_bounds__(kGWaves * kWave) void k_layer_gemm(
 // of 32 or no tile divides the rows).
 LayerPlan layer_plan(int n0, int n1, int N, int K, int M, bool glu, size_t part_floats) {
   LayerPlan best{0, 1};
-  if (K % kGK != 0 || M < 1) return best;
-  const int nk = K / kGK, slots = 8 * kGPerXcd;
+  if (M < 1) return best;
+  const int slots = 8 * kGPerXcd;
   double tbest = 0.0;
   for (int bn = 128; bn <= 256; bn *= 2) {
     if (N % bn != 0 || n0 % bn != 0 || n1 % bn != 0) continue;
+    const int gk = bn == 128 ? 64 : 32, nk = K / gk;    // k per stage, stages
+    if (K % gk != 0) continue;
     const double rate = bn == 128 ? 3.6e12 : 4.3e12;
     const long tiles = (long)(N / bn) * ((M + bn - 1) / bn);
     for (int S = 1; S <= (glu ? 1 : kLayerSplitMax); ++S) {
-      if (nk % S != 0 || (S > 1 && nk / S < 16)) continue;
+      if (nk % S != 0 || (S > 1 && nk / S < 512 / gk)) continue;
       if (S > 1 && (double)S * M * N > (double)part_floats) continue;
       const long items = tiles * S;
       const double rounds = (double)((items + slots - 1) / slots);
@@ -207,7 +209,7 @@ hipError_t launch_layer_gemm(LayerPlan pl, const uint16_t* W0, const uint16_t* W
                              const uint16_t* W2, int n0, int n1, int N, int K, const uint16_t* X,
                              int M, const float* R, int ldr, float* Y, uint16_t* Yb, int ldy,
                              hipStream_t st) {
-  if ((pl.bn != 128 && pl.bn != 256) || pl.S < 1 || K % (pl.S * kGK) != 0 || N % pl.bn != 0 ||
+  if ((pl.bn != 128 && pl.bn != 256) || pl.S < 1 || K % (pl.S * (pl.bn == 128 ? 64 : 32)) != 0 || N % pl.bn != 0 ||
       n0 % pl.bn != 0 || n1 % pl.bn != 0 || (pl.S > 1 && (R || Yb || !Y || ldy != N)))
     return hipErrorInvalidValue;
   launch<false>(pl, W0, W1, W2, n0, n1, N, K, X, M, R, ldr, Y, Yb, ldy, st);
@@ -216,7 +218,7 @@ hipError_t launch_layer_gemm(LayerPlan pl, const uint16_t* W0, const uint16_t* W
 
 hipError_t launch_layer_glu(LayerPlan pl, const uint16_t* Wg, const uint16_t* Wu, int F, int K,
                             const uint16_t* X, int M, uint16_t* act, int ldy, hipStream_t st) {
-  if ((pl.bn != 128 && pl.bn != 256) || pl.S != 1 || K % kGK != 0 || (2 * F) % pl.bn != 0 ||
+  if ((pl.bn != 128 && pl.bn != 256) || pl.S != 1 || K % 64 != 0 || (2 * F) % pl.bn != 0 ||
       F % pl.bn != 0)
     return hipErrorInvalidValue;
   launch<true>(pl, Wg, Wu, Wu, F, F, 2 * F, K, X, M, nullptr, 0, nullptr, act, ldy, st);
