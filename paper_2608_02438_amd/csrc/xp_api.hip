@@ -323,7 +323,7 @@ extern "C" xp_status xp_refine_block(xp_handle* h, int32_t batch, const void* hi
   XP_TIMED(XP_STAGE_PREP, launch_prep(h, batch, hidden, temp, temperature, st));
   if (filtering) XP_TIMED(XP_STAGE_PREP, launch_filter_params(h, batch, temp, top_k, top_p, st));
   XP_TIMED(XP_STAGE_LMHEAD, launch_lmhead(h, batch * h->B, hidden, temp, st));
-  const bool fused = K > 0 && pass_fused_ok(h, temp);
+  const bool fused = K > 0 && pass_fused_ok(h, batch, temp);
   if (!fused)
     XP_TIMED(XP_STAGE_SELECT,
              launch_select(h, batch, -1, K, flags, seed_ids, temp, u_draft, out_traj,

@@ -123,7 +123,7 @@ hipError_t launch_vfilter(xp_handle* h, int batch, const int32_t* draft, const f
                           hipStream_t st);
 hipError_t launch_rspace(xp_handle* h, int batch, int pass, uint32_t flags, const int32_t* anchor,
                          bool front, hipStream_t st);
-bool pass_fused_ok(const xp_handle* h, const uint8_t* temp);
+bool pass_fused_ok(const xp_handle* h, int batch, const uint8_t* temp);
 int gemm_units(const xp_handle* h, int M);
 // the context layer's projections for many positions (xp_lgemm.hip): tile
 // size bn (128 or 256; 0: no plan) and S k splits; with S > 1 the launch

@@ -10,29 +10,35 @@
 // write the 16 feature dims [16 rt, 16 rt + 16) of c for the residual of
 // Trans, and workgroup 0 does the bookkeeping of the selection (iterate,
 // trajectory, fixed-point test).  Used for all-greedy batches with blocks of
-// at most 16 positions and bf16 weights; other batches take the separate
-// select / fusemix / trans1 kernels, which compute the same values.
+// at most 16 positions; other batches take the separate select / fusemix /
+// trans1 kernels, which compute the same values.  A block of at most 8
+// positions (BP = 8) stages 28 of the 120 pairs of L.  With fp32 weights (blocks
+// of 8, 8 passes, batch 1) one kernel instead of three takes the step from 180 to
+// 157 us.
 #include "xp_internal.h"
 #include "xp_split.h"
 
 namespace xp {
 
 constexpr int kPassUnits = 256;      // most key units per position
-constexpr int kPassPairs = 120;      // L pairs of a 16-position block
 
+template <typename T, int BP>
 __global__ __launch_bounds__(256) void k_pass(
     int mode, int pass, int batch, int B, int V, int M, const uint64_t* __restrict__ keys,
     int nkeys, const int32_t* __restrict__ seed_ids, const float* __restrict__ Pa,
-    const float* __restrict__ Ttab, const uint16_t* __restrict__ Lp,
+    const float* __restrict__ Ttab, const T* __restrict__ Lp,
     const int32_t* __restrict__ anchor, const int32_t* __restrict__ Yprev,
     int32_t* __restrict__ Ynew, int32_t* __restrict__ traj, int32_t* __restrict__ iters,
     int32_t* __restrict__ ctrl, uint32_t* __restrict__ err, int early_exit,
-    const uint16_t* __restrict__ W1, float* __restrict__ c, float* __restrict__ h1) {
+    const T* __restrict__ W1, float* __restrict__ c, float* __restrict__ h1) {
   constexpr int r = 256, r2 = 512, CS = r + 4;
+  constexpr bool kBf = sizeof(T) == 2;
+  constexpr int kPairs = BP * (BP - 1) / 2;          // L pairs of a block
   constexpr int KPT = kPassUnits * 16 / 256;         // keys per thread
-  constexpr int LPT = kPassPairs * r * 2 / 16 / 256; // 16-byte L chunks per thread
+  constexpr int LCP = r * (int)sizeof(T) / 16;       // 16-byte L chunks per pair
+  constexpr int LPT = (kPairs * LCP + 255) / 256;    // and per thread
   __shared__ float A[16][CS];                        // a_k, then c_k
-  __shared__ u32x4 Ls[kPassPairs * r * 2 / 16];      // L of the block (60 KB)
+  __shared__ u32x4 Ls[kPairs * LCP];                 // L of the block (up to 60 KB, fp32 120 KB)
   __shared__ uint64_t kred[4][16];
   __shared__ int ys[16];
   __shared__ int chg;
@@ -60,7 +66,7 @@ __global__ __launch_bounds__(256) void k_pass(
     const int i = (tid >> 4) + 16 * j;
     kv[j] = keys[(size_t)(i < nkeys ? i : nkeys - 1) * M + (size_t)b * B + kkc];
   }
-  const int nch = (B * (B - 1) / 2) * (r * 2 / 16);
+  const int nch = (B * (B - 1) / 2) * LCP;
   u32x4 lc[LPT];
   const u32x4* lsrc = reinterpret_cast<const u32x4*>(Lp);
 #pragma unroll
@@ -69,10 +75,13 @@ __global__ __launch_bounds__(256) void k_pass(
     lc[j] = lsrc[q < nch ? q : (nch > 0 ? nch - 1 : 0)];
   }
   const int k0 = wave * (r / 4);                                // W_1 k slice of the wave
-  const uint16_t* arow = W1 + (size_t)(rt * 16 + li) * r + k0;
-  u32x4 w[2];
+  // the wave's W_1 fragments, in the order of trans1: bf16 two 32-k steps, fp32
+  // four 16-k steps
+  constexpr int KS = kBf ? 32 : 16, NW = 64 / KS;
+  const T* arow = W1 + (size_t)(rt * 16 + li) * r + k0;
+  u32x4 w[NW];
 #pragma unroll
-  for (int u = 0; u < 2; ++u) w[u] = ld16(arow + u * 32 + 8 * g);
+  for (int u = 0; u < NW; ++u) w[u] = ld16(arow + u * KS + KS / 4 * g);
   const int pk = tid >> 4, pkc = pk < B ? pk : B - 1;          // gather role: position pk
   const int d0 = (tid & 15) * 16;
   float4 pa[4];
@@ -159,16 +168,16 @@ __global__ __launch_bounds__(256) void k_pass(
   //     the triangle is unrolled so that all its LDS reads are in flight -----
   {
     const int d = tid;
-    const uint16_t* ls = reinterpret_cast<const uint16_t*>(Ls);
-    float a[16];
+    const T* ls = reinterpret_cast<const T*>(Ls);
+    float a[BP];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) a[k] = A[k][d];
+    for (int k = 0; k < BP; ++k) a[k] = A[k][d];
 #pragma unroll
-    for (int k = 1; k < 16; ++k) {
+    for (int k = 1; k < BP; ++k) {
       if (k < B) {
         float acc = a[k];
 #pragma unroll
-        for (int i = 0; i < k; ++i) acc += bf16_to_f32(ls[(k * (k - 1) / 2 + i) * r + d]) * a[i];
+        for (int i = 0; i < k; ++i) acc += to_f32(ls[(k * (k - 1) / 2 + i) * r + d]) * a[i];
         A[k][d] = acc;
       }
     }
@@ -182,11 +191,15 @@ __global__ __launch_bounds__(256) void k_pass(
   // --- h1 rows [16 rt, 16 rt + 16) = silu(W_1 c) ------------------------------
   floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const float* crow = &A[li][k0 + u * 32 + 8 * g];
+  for (int u = 0; u < NW; ++u) {
+    const float* crow = &A[li][k0 + u * KS + KS / 4 * g];
     const float4 x0 = *reinterpret_cast<const float4*>(crow);
-    const float4 x1 = *reinterpret_cast<const float4*>(crow + 4);
-    acc = mma_split_b(w[u], x0, x1, acc);
+    if constexpr (kBf) {
+      const float4 x1 = *reinterpret_cast<const float4*>(crow + 4);
+      acc = mma_split_b(w[u], x0, x1, acc);
+    } else {
+      acc = mma4(__builtin_bit_cast(float4, w[u]), x0, acc);
+    }
   }
   red[wave][lane] = acc;
   __syncthreads();
@@ -207,8 +220,17 @@ __global__ __launch_bounds__(256) void k_pass(
 
 // ---------------------------------------------------------------------------
 // Call after the A1 launch of the same refine (it sets the unit count).
-bool pass_fused_ok(const xp_handle* h, const uint8_t* temp) {
-  return temp == nullptr && h->dtype == XP_BF16 && h->B <= 16 && h->lm_units_cur <= kPassUnits &&
+//
+// fp32: as long as the 32 workgroups of every sequence run in one round (their
+// LDS, mostly L, lets 3 share a CU with blocks of at most 8 positions and 1 with
+// longer ones); past that every round repeats Fuse and Mix 32 times a sequence
+// and the separate kernels win.  A greedy step of 8 passes at H = 256, V = 1024,
+// separate against fused: blocks of 8, batch 1 / 8 / 16 / 64 200 / 204 / 215 /
+// 319 against 165 / 168 / 186 / 351 us; blocks of 16, batch 1 / 8 / 16 / 64 204
+// / 206 / 217 / 437 against 182 / 187 / 240 / 693 us.
+bool pass_fused_ok(const xp_handle* h, int batch, const uint8_t* temp) {
+  if (h->dtype == XP_F32 && batch * 32 > h->cus * (h->B <= 8 ? 3 : 1)) return false;
+  return temp == nullptr && h->B <= 16 && h->lm_units_cur <= kPassUnits &&
          h->read_wgs <= kPassUnits;
 }
 
@@ -221,10 +243,19 @@ hipError_t launch_pass(xp_handle* h, int batch, int pass, uint32_t flags, const 
   int32_t* traj = out_traj ? out_traj + (size_t)pass * M : nullptr;
   const int nkeys = mode == 0 ? h->lm_units_cur : h->read_wgs;
   const int early = (flags & XP_EARLY_EXIT) ? 1 : 0;
-  hipLaunchKernelGGL(k_pass, dim3(batch, 32), dim3(256), 0, st, mode, pass, batch, h->B, h->V, M,
-                     h->ws.keys, nkeys, mode == 0 ? seed_ids : nullptr, h->ws.Pa, h->ws.T,
-                     (const uint16_t*)h->ws.Lp, anchor, Yprev, Ynew, traj, h->ws.iters,
-                     h->ws.ctrl, h->ws.err, early, (const uint16_t*)h->W_1, h->ws.c, h->ws.h1);
+#define XP_PASS(TT, PP)                                                                         \
+  hipLaunchKernelGGL((k_pass<TT, PP>), dim3(batch, 32), dim3(256), 0, st, mode, pass, batch, h->B, \
+                     h->V, M, h->ws.keys, nkeys, mode == 0 ? seed_ids : nullptr, h->ws.Pa,      \
+                     h->ws.T, (const TT*)h->ws.Lp, anchor, Yprev, Ynew, traj, h->ws.iters,      \
+                     h->ws.ctrl, h->ws.err, early, (const TT*)h->W_1, h->ws.c, h->ws.h1)
+  if (h->dtype == XP_BF16) {
+    if (h->B <= 8) XP_PASS(uint16_t, 8);
+    else XP_PASS(uint16_t, 16);
+  } else {
+    if (h->B <= 8) XP_PASS(float, 8);
+    else XP_PASS(float, 16);
+  }
+#undef XP_PASS
   return hipGetLastError();
 }
 

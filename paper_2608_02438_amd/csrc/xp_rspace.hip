@@ -20,14 +20,6 @@ __device__ __forceinline__ float4 load4f(const uint16_t* p) {
   return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u),
                      __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xFFFF0000u));
 }
-__device__ __forceinline__ floatx4 mma4(float4 a, float4 b, floatx4 c) {
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b.z, c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b.w, c, 0, 0, 0);
-  return c;
-}
-
 // ---------------------------------------------------------------------------
 // k_prep: part[mat][ks][m][o] = F_mat[o][slice ks] . h[m][slice ks] for
 // F_0 = W_in[:,0:r] W_h and F_1 = W_in[:,r:2r] W_g (fp32 [r][H]); the KSP

@@ -57,4 +57,13 @@ __device__ __forceinline__ floatx4 mma_split_a(float4 x0, float4 x1, u32x4 b, fl
   return acc;
 }
 
+// acc += a . b over one 16-k step in fp32 (four 4-k steps): fp32 weights.
+__device__ __forceinline__ floatx4 mma4(float4 a, float4 b, floatx4 c) {
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b.z, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b.w, c, 0, 0, 0);
+  return c;
+}
+
 }  // namespace xp
