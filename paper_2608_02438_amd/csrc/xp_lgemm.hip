@@ -153,14 +153,14 @@ __global__ __launch_bounds__(kGWaves * kWave) void k_layer_gemm(
 
 // Tile size and k splits of one projection: among 128 x 128 and 256 x 256
 // tiles (BN dividing every stacked weight's rows) and S = 1 .. kLayerSplitMax
-// splits (S dividing the k steps, at least 16 k steps per split, S M N fp32
+// splits (S dividing the stages of 64 or 32 k, at least 512 k per split, S M N fp32
 // slab values within part_floats; GLU: S = 1), the one with the least
 // estimated time: rounds of one work item per workgroup of the persistent
 // grid, an item costing 17 us plus its flops at 3.6 TFLOP/s per CU on 128 x
 // 128 tiles or 4.3 on 256 x 256 (fitted to the measured launches of the
 // Qwen3-8B projections at 128 to 2048 positions), plus one read of the slabs
 // at 5 TB/s by the kernel that adds them.  bn = 0: no plan (K not a multiple
-// of 32 or no tile divides the rows).
+// of the stage or no tile divides the rows).
 LayerPlan layer_plan(int n0, int n1, int N, int K, int M, bool glu, size_t part_floats) {
   LayerPlan best{0, 1};
   if (M < 1) return best;
@@ -209,8 +209,8 @@ hipError_t launch_layer_gemm(LayerPlan pl, const uint16_t* W0, const uint16_t* W
                              const uint16_t* W2, int n0, int n1, int N, int K, const uint16_t* X,
                              int M, const float* R, int ldr, float* Y, uint16_t* Yb, int ldy,
                              hipStream_t st) {
-  if ((pl.bn != 128 && pl.bn != 256) || pl.S < 1 || K % (pl.S * (pl.bn == 128 ? 64 : 32)) != 0 || N % pl.bn != 0 ||
-      n0 % pl.bn != 0 || n1 % pl.bn != 0 || (pl.S > 1 && (R || Yb || !Y || ldy != N)))
+  if ((pl.bn != 128 && pl.bn != 256) || pl.S < 1 ||
+      K % (pl.S * (pl.bn == 128 ? 64 : 32)) != 0 || N % pl.bn != 0 || n0 % pl.bn != 0 || n1 % pl.bn != 0 || (pl.S > 1 && (R || Yb || !Y || ldy != N)))
     return hipErrorInvalidValue;
   launch<false>(pl, W0, W1, W2, n0, n1, N, K, X, M, R, ldr, Y, Yb, ldy, st);
   return hipGetLastError();
