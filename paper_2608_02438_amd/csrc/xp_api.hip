@@ -328,10 +328,10 @@ extern "C" xp_status xp_refine_block(xp_handle* h, int32_t batch, const void* hi
     XP_TIMED(XP_STAGE_SELECT,
              launch_select(h, batch, -1, K, flags, seed_ids, temp, u_draft, out_traj,
                            K == 0 ? out_ids : nullptr, K == 0 ? out_iters : nullptr, st,
-                           filtering));
+                           filtering, false));
   for (int j = 0; j < K; ++j) {
     if (fused) XP_TIMED(XP_STAGE_RSPACE, launch_pass(h, batch, j, flags, seed_ids, anchor, out_traj, st));
-    XP_TIMED(XP_STAGE_RSPACE, launch_rspace(h, batch, j, flags, anchor, !fused, st));
+    XP_TIMED(XP_STAGE_RSPACE, launch_rspace(h, batch, j, flags, anchor, !fused, j > 0, temp, out_traj, st));
     // out_logits holds the last executed pass's logits, so only the last pass
     // writes them (2048 positions: 5 x 580 us of stores less).  With the early
     // exit that pass then reads every row, those at their fixed point among
@@ -344,7 +344,7 @@ extern "C" xp_status xp_refine_block(xp_handle* h, int32_t batch, const void* hi
       XP_TIMED(XP_STAGE_SELECT,
                launch_select(h, batch, j, K, flags, nullptr, temp, u_draft, out_traj,
                              lastp ? out_ids : nullptr, lastp ? out_iters : nullptr, st,
-                             filtering));
+                             filtering, !lastp));
   }
   if (K == 0 && (flags & XP_WRITE_LOGITS))
     XP_LAUNCH(launch_base_logits(h, batch, out_logits, st));

@@ -111,7 +111,7 @@ hipError_t launch_lmhead(xp_handle* h, int M, const void* hidden, const uint8_t*
 hipError_t launch_select(xp_handle* h, int batch, int pass, int K, uint32_t flags,
                          const int32_t* seed_ids, const uint8_t* temp, const float* u_draft,
                          int32_t* out_traj, int32_t* out_ids, int32_t* out_iters,
-                         hipStream_t st, bool filtering);
+                         hipStream_t st, bool filtering, bool pick_only);
 // truncated sampling (xp_filter.hip)
 hipError_t launch_filter_params(xp_handle* h, int batch, const uint8_t* temp, const int32_t* top_k,
                                 const float* top_p, hipStream_t st);
@@ -122,7 +122,8 @@ hipError_t launch_vfilter(xp_handle* h, int batch, const int32_t* draft, const f
                           const float* racc, const float* ures, int32_t* out_n, int32_t* out_next,
                           hipStream_t st);
 hipError_t launch_rspace(xp_handle* h, int batch, int pass, uint32_t flags, const int32_t* anchor,
-                         bool front, hipStream_t st);
+                         bool front, bool sel, const uint8_t* temp, int32_t* out_traj,
+                         hipStream_t st);
 bool pass_fused_ok(const xp_handle* h, int batch, const uint8_t* temp);
 int gemm_units(const xp_handle* h, int M);
 // the context layer's projections for many positions (xp_lgemm.hip): tile

@@ -251,13 +251,37 @@ __global__ __launch_bounds__(256) void k_prep_sum(int B, int M, int ksp,
 // Fuse (gather form) and Mix for 16 feature dims d of one sequence.  Mix is
 // independent per d (eq. mix: c^(d) = (I + L^(d)) a^(d)), so the 16 dims of a
 // workgroup need only their own 16 columns of every L^(d).
+//
+// sel: the kernel also makes the selection of pass `pass - 1` (k_select's, with
+// its bookkeeping by workgroup (b, 0)): every workgroup of a sequence takes the
+// tokens itself, from the sampler's choice or the maximum over the key rows.
+// One launch of 4 to 6 us less per pass in the chain; the 16 workgroups' repeated
+// maxima (32 KB of keys each, 64 KB with blocks of 32) cost less: a step of 128
+// sampled positions 730 -> 722 us, 512 greedy ones 1373 -> 1363, 33 fp32 ones
+// 435 -> 425, 2048 greedy ones 3185 -> 3191 (in the noise), one block of 32 at
+// V = 1024 195 -> 182.  The seed keeps k_select: the LM head leaves up to 2400
+// key rows.
 template <typename T, int BP>
 __global__ __launch_bounds__(256) void k_fusemix(
     int B, int V, int M, const float* __restrict__ Pa, const float* __restrict__ Ttab,
-    const T* __restrict__ Lp, const int32_t* __restrict__ anchor, const int32_t* __restrict__ Y,
-    float* __restrict__ c, uint32_t* __restrict__ err, const int32_t* __restrict__ iters,
-    int skip_when_done) {
-  if (skip_when_done && iters[blockIdx.x]) return;    // the sequence is at its fixed point
+    const T* __restrict__ Lp, const int32_t* __restrict__ anchor, int32_t* Y,
+    float* __restrict__ c, uint32_t* __restrict__ err, int32_t* iters,
+    int skip_when_done, int sel, int pass, int batch, const uint64_t* __restrict__ keys, int nkeys,
+    const uint8_t* __restrict__ temp, const int32_t* __restrict__ Yprev,
+    int32_t* __restrict__ traj, int32_t* __restrict__ ctrl) {
+  // (workgroup (b, 0) may set iters[b] below while others of the sequence have
+  // yet to read it: only when the sequence has just reached its fixed point,
+  // and then with the early exit all of them return here or there)
+  const int it0 = iters[blockIdx.x];
+  if (skip_when_done && it0) {                        // the sequence is at its fixed point
+    if (sel && blockIdx.y == 0 && threadIdx.x < B) {  // its block carries over
+      const size_t p = (size_t)blockIdx.x * B + threadIdx.x;
+      const int y = Yprev[p];
+      Y[p] = y;
+      if (traj) traj[p] = y;
+    }
+    return;
+  }
   constexpr int r = 256;
   constexpr int EPT = BP / 16;                       // positions per thread
   constexpr int NPAIR = BP * (BP - 1) / 2;
@@ -265,6 +289,9 @@ __global__ __launch_bounds__(256) void k_fusemix(
   constexpr int LCH_T = (NPAIR * CPP + 255) / 256;   // chunks per thread
   __shared__ float A[BP][17];
   __shared__ u32x4 Ls[NPAIR * CPP > 0 ? NPAIR * CPP : 1];
+  __shared__ uint64_t sbest[4][BP];
+  __shared__ int ys[BP];
+  __shared__ int chg;
   const int b = blockIdx.x, dt = blockIdx.y, tid = threadIdx.x;
   const int dl = tid & 15, kg = tid >> 4, d = dt * 16 + dl;
   const int npair = B * (B - 1) / 2, nch = npair * CPP;
@@ -289,6 +316,59 @@ __global__ __launch_bounds__(256) void k_fusemix(
     pa[j] = Pa[m * r + d];
     xv[j] = Y[kc == 0 ? m : m - 1];
     if (kc == 0) xv[j] = ya;
+  }
+  if (sel) {                                         // workgroup-uniform
+    const bool sample = temp != nullptr && temp[b] != 0;
+    const int yo = tid < B ? Y[(size_t)b * B + tid] : 0, yp = tid < B ? Yprev[(size_t)b * B + tid] : 0;
+    if (!sample) {
+      constexpr int NRG = 256 / BP, kRows = 16;
+      const int pos = tid % BP, rg = tid / BP;
+      const size_t col = (size_t)b * B + (pos < B ? pos : B - 1);
+      uint64_t best = 0;
+      for (int r0 = rg; r0 < nkeys; r0 += kRows * NRG) {
+        uint64_t kv[kRows];
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) {
+          const int row = r0 + j * NRG;              // rows past nkeys repeat the last
+          kv[j] = keys[(size_t)(row < nkeys ? row : nkeys - 1) * M + col];
+        }
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) best = umax64(best, kv[j]);
+      }
+#pragma unroll
+      for (int o = BP; o < kWave; o <<= 1) best = umax64(best, shfl_xor_u64(best, o));
+      if ((tid & (kWave - 1)) < BP) sbest[tid / kWave][pos] = best;
+    }
+    if (tid == 0) chg = 0;
+    __syncthreads();
+    if (tid < B) {
+      int y = yo;                                    // the sampler's choice
+      if (!sample) {
+        uint64_t bb = sbest[0][tid];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) bb = umax64(bb, sbest[w][tid]);
+        y = (int)key_index(bb);
+      }
+      ys[tid] = y;
+      if (y != yp) atomicOr(&chg, 1);
+      if (dt == 0) {
+        const size_t p = (size_t)b * B + tid;
+        Y[p] = y;
+        if (traj) traj[p] = y;
+      }
+    }
+    __syncthreads();
+    const bool now_fixed = chg == 0 && it0 == 0;
+    if (now_fixed && dt == 0 && tid == 0) {
+      iters[b] = pass;                               // the selection of pass `pass - 1`
+      if (atomicAdd(&ctrl[0], 1) + 1 == batch) ctrl[1] = 1;
+    }
+    if (skip_when_done && now_fixed) return;         // whole workgroup
+#pragma unroll
+    for (int j = 0; j < EPT; ++j) {
+      const int k = kg + 16 * j, kc = k < B ? k : B - 1;
+      if (kc > 0) xv[j] = ys[kc - 1];
+    }
   }
   bool bad = false;
 #pragma unroll
@@ -603,17 +683,21 @@ hipError_t launch_prep(xp_handle* h, int batch, const void* hidden, const uint8_
 }
 
 // front = false launches only the second Trans product (the fused pass kernel
-// has already produced c and h1).
+// has already produced c and h1).  sel: the front half makes the selection of
+// the previous pass too.
 template <typename T, int BP>
 static void rspace_t(xp_handle* h, int batch, int pass, int skip, const int32_t* anchor,
-                     bool front, hipStream_t st) {
+                     bool front, bool sel, const uint8_t* temp, int32_t* out_traj,
+                     hipStream_t st) {
   const int M = batch * h->B;
   const bool tiled = sizeof(T) == 2 && M >= kTransTiled;
   const dim3 tgrid1(512 / 64, (M + kTransPT - 1) / kTransPT), tgrid2(256 / 64, tgrid1.y);
   if (front) {
     hipLaunchKernelGGL((k_fusemix<T, BP>), dim3(batch, 16), dim3(256), 0, st, h->B, h->V, M,
                        h->ws.Pa, h->ws.T, (const T*)h->ws.Lp, anchor, h->ws.Y[pass % 2], h->ws.c,
-                       h->ws.err, h->ws.iters, skip);
+                       h->ws.err, h->ws.iters, skip, sel ? 1 : 0, pass, batch, h->ws.keys,
+                       h->read_wgs, temp, h->ws.Y[(pass + 1) % 2],
+                       out_traj ? out_traj + (size_t)pass * M : nullptr, h->ws.ctrl);
     if (tiled)
       hipLaunchKernelGGL((k_trans_tiled<256, 0>), tgrid1, dim3(256), 0, st,
                          (const uint16_t*)h->W_1, h->ws.c, M, h->ws.c, h->ws.h1,
@@ -632,18 +716,19 @@ static void rspace_t(xp_handle* h, int batch, int pass, int skip, const int32_t*
 }
 
 hipError_t launch_rspace(xp_handle* h, int batch, int pass, uint32_t flags, const int32_t* anchor,
-                         bool front, hipStream_t st) {
+                         bool front, bool sel, const uint8_t* temp, int32_t* out_traj,
+                         hipStream_t st) {
   const int skip = (flags & XP_EARLY_EXIT) ? 1 : 0;
   if (h->dtype == XP_BF16) {
     if (h->B <= 16)
-      rspace_t<uint16_t, 16>(h, batch, pass, skip, anchor, front, st);
+      rspace_t<uint16_t, 16>(h, batch, pass, skip, anchor, front, sel, temp, out_traj, st);
     else
-      rspace_t<uint16_t, 32>(h, batch, pass, skip, anchor, front, st);
+      rspace_t<uint16_t, 32>(h, batch, pass, skip, anchor, front, sel, temp, out_traj, st);
   } else {
     if (h->B <= 16)
-      rspace_t<float, 16>(h, batch, pass, skip, anchor, front, st);
+      rspace_t<float, 16>(h, batch, pass, skip, anchor, front, sel, temp, out_traj, st);
     else
-      rspace_t<float, 32>(h, batch, pass, skip, anchor, front, st);
+      rspace_t<float, 32>(h, batch, pass, skip, anchor, front, sel, temp, out_traj, st);
   }
   return hipGetLastError();
 }

@@ -310,7 +310,7 @@ __global__ __launch_bounds__(256) void k_base_rows(int M, int V, const float* __
 hipError_t launch_select(xp_handle* h, int batch, int pass, int K, uint32_t flags,
                          const int32_t* seed_ids, const uint8_t* temp, const float* u_draft,
                          int32_t* out_traj, int32_t* out_ids, int32_t* out_iters,
-                         hipStream_t st, bool filtering) {
+                         hipStream_t st, bool filtering, bool pick_only) {
   const int M = batch * h->B;
   const int mode = pass < 0 ? 0 : 1;
   int32_t* Yprev = h->ws.Y[(pass + 2) % 2];      // pass j reads Y[j % 2]
@@ -355,6 +355,7 @@ hipError_t launch_select(xp_handle* h, int batch, int pass, int K, uint32_t flag
 #undef XP_SMP_CH
 #undef XP_SMP
   }
+  if (pick_only) return hipGetLastError();         // the next pass's k_fusemix selects
   if (h->dtype == XP_BF16)
     hipLaunchKernelGGL((k_select<uint16_t>), dim3(batch), dim3(kSelWaves * kWave), 0, st, mode, pass, batch,
                        h->B, h->V, M, h->ws.s, M, (const uint16_t*)h->W_r,
