@@ -221,15 +221,18 @@ __global__ __launch_bounds__(256) void k_pass(
 // ---------------------------------------------------------------------------
 // Call after the A1 launch of the same refine (it sets the unit count).
 //
-// fp32: as long as the 32 workgroups of every sequence run in one round (their
-// LDS, mostly L, lets 3 share a CU with blocks of at most 8 positions and 1 with
-// longer ones); past that every round repeats Fuse and Mix 32 times a sequence
-// and the separate kernels win.  A greedy step of 8 passes at H = 256, V = 1024,
-// separate against fused: blocks of 8, batch 1 / 8 / 16 / 64 200 / 204 / 215 /
-// 319 against 165 / 168 / 186 / 351 us; blocks of 16, batch 1 / 8 / 16 / 64 204
-// / 206 / 217 / 437 against 182 / 187 / 240 / 693 us.
+// It runs as long as the 32 workgroups of every sequence fit on the CUs at once
+// (their LDS, mostly L, lets 4 (fp32 3) share a CU with blocks of at most 8
+// positions and 1 with longer ones); past that every round repeats Fuse and Mix 32
+// times a sequence and the separate kernels win.  A greedy step of 8 passes at
+// H = 256, V = 1024, separate against fused: bf16 blocks of 16, batch 8 / 12 / 16 /
+// 64 186 / 217 / 219 / 423 against 173 / 242 / 245 / 657 us; bf16 blocks of 8,
+// batch 16 / 32 / 48 / 64 188 / 233 / 278 / 319 against 169 / 227 / 283 / 334 us;
+// fp32 blocks of 16, batch 8 / 16 206 / 217 against 187 / 240 us; fp32 blocks of 8,
+// batch 1 / 16 / 64 200 / 215 / 319 against 165 / 186 / 351 us.
 bool pass_fused_ok(const xp_handle* h, int batch, const uint8_t* temp) {
-  if (h->dtype == XP_F32 && batch * 32 > h->cus * (h->B <= 8 ? 3 : 1)) return false;
+  const int per_cu = h->B <= 8 ? (h->dtype == XP_BF16 ? 4 : 3) : 1;
+  if (batch * 32 > h->cus * per_cu) return false;
   return temp == nullptr && h->B <= 16 && h->lm_units_cur <= kPassUnits &&
          h->read_wgs <= kPassUnits;
 }

@@ -1,12 +1,12 @@
-"""The fused front half of a greedy pass with fp32 weights and with short blocks
+"""The fused front half of a greedy pass: both weight types, short and long blocks
 (needs an MI355X).
 
 An all-greedy call runs selection, Fuse, Mix and the first Trans product as one
 kernel; an all-zero temperature vector sends the same rows through the separate
 kernels.  Both add in the same order, so every output agrees bit for bit.
 Sizes: blocks on both sides of 8 positions and at 1, 2 and 16, and batches on
-both sides of the one-round rule of the fp32 form (256 CUs: 24 sequences of up
-to 8 positions, 8 of longer ones)."""
+both sides of the one-round rule (256 CUs: 24 fp32 or 32 bf16 sequences of up to 8
+positions, 8 of longer ones)."""
 import numpy as np
 import pytest
 
@@ -20,7 +20,8 @@ STRESS = dict(W_e=1.0, W_r=0.3, L=0.3, W_in=0.08, W_1=0.08, W_2=0.06)
 @pytest.mark.parametrize("dtype,B,batch,seeded", [
     ("f32", 1, 1, False), ("f32", 2, 3, True), ("f32", 8, 1, True), ("f32", 8, 24, False),
     ("f32", 8, 25, False), ("f32", 9, 2, False), ("f32", 9, 9, True), ("f32", 16, 1, False),
-    ("f32", 16, 8, True), ("bf16", 1, 2, False), ("bf16", 7, 4, True), ("bf16", 8, 2, False)])
+    ("f32", 16, 8, True), ("bf16", 1, 2, False), ("bf16", 7, 4, True), ("bf16", 8, 2, False),
+    ("bf16", 8, 32, False), ("bf16", 8, 33, True), ("bf16", 16, 8, False), ("bf16", 16, 9, False)])
 def test_fused_pass_equals_separate_kernels(dtype, B, batch, seeded):
     import torch
     print(f"fused pass: {dtype} B={B} batch={batch} seeded={seeded}", flush=True)
