@@ -331,7 +331,8 @@ extern "C" xp_status xp_refine_block(xp_handle* h, int32_t batch, const void* hi
                            filtering, false));
   for (int j = 0; j < K; ++j) {
     if (fused) XP_TIMED(XP_STAGE_RSPACE, launch_pass(h, batch, j, flags, seed_ids, anchor, out_traj, st));
-    XP_TIMED(XP_STAGE_RSPACE, launch_rspace(h, batch, j, flags, anchor, !fused, j > 0, temp, out_traj, st));
+    XP_TIMED(XP_STAGE_RSPACE,
+             launch_rspace(h, batch, j, flags, anchor, !fused, j > 0, temp, out_traj, st));
     // out_logits holds the last executed pass's logits, so only the last pass
     // writes them (2048 positions: 5 x 580 us of stores less).  With the early
     // exit that pass then reads every row, those at their fixed point among

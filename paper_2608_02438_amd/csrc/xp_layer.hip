@@ -431,8 +431,9 @@ __global__ __launch_bounds__(kGsWaves * kWave) void k_gemv_sk(
 // ---------------------------------------------------------------------------
 // QK-norm + RoPE: gridDim.y workgroups per position m (more for few positions,
 // where a wave's slots one after the other are all the time there is); wave w of
-// workgroup y takes the head slots 4 y + w, + 4 gridDim.y, ...: slots [0, nh) are the q heads, [nh, nh + nkv) the k heads,
-// [nh + nkv, nh + 2 nkv) the v heads (converted only).  Lane l holds elements
+// workgroup y takes the head slots 4 y + w, + 4 gridDim.y, ...: slots [0, nh) are
+// the q heads, [nh, nh + nkv) the k heads, [nh + nkv, nh + 2 nkv) the v heads
+// (converted only).  Lane l holds elements
 // l and l + 64, the rotate-half pair of frequency l; the angle (taken in double,
 // lt = log2 theta) depends on the position and l only, so each wave forms its cosine
 // and sine once for all its slots.  The row is P_0 + ... + P_{S-1}
@@ -513,8 +514,8 @@ __global__ __launch_bounds__(256) void k_qkrope(
 // 512 to 16384 keys running alone), and the partials are at most W + segments -
 // 1.  Bound by the loop's LDS reads, vector and matrix operations together more
 // than by HBM: batch 32 x 16 at 8192 keys 252 -> 204 us (5.3 TB/s), batch 64 x 32
-// at 512 .. 16384 keys 832 -> 581 us (3.8 TB/s), batch 8 x 16 at 4096 43 -> 32 us.  Wave w is query head kvh * GRP +
-// w % GRP for the block positions 16 pb .. 16 pb + 15, pb = w / GRP (NPB
+// at 512 .. 16384 keys 832 -> 581 us (3.8 TB/s), batch 8 x 16 at 4096 43 -> 32 us.
+// Wave w is query head kvh * GRP + w % GRP for the block positions 16 pb .. 16 pb + 15, pb = w / GRP (NPB
 // position blocks), so the group's query heads and the block's positions share
 // every K and V byte read.
 // Key kk of sequence b is context key kk (kk < C) or block key kk - C
