@@ -337,10 +337,9 @@ const char* xp_layer_last_error(const xp_layer* L);
  * streams, or two host threads) race and give undefined results; calls
  * ordered on one stream are safe.  Output equals xp_layer_forward's bit for
  * bit for calls of up to 64 positions whose attention partials fit beside
- * the other buffers at the default number of shares.  Otherwise only the fp32
- * summation order differs: the context may be read in fewer, longer shares
- * (fewer partials), and above 64 positions the projections run without the k
- * splits that xp_layer_forward may use.
+ * the other buffers.  Otherwise only the fp32 summation order differs: the
+ * contexts may be read in fewer, longer parts, and above 64 positions the
+ * projections run without the k splits that xp_layer_forward may use.
  *
  * Limits: batch * B positions whose buffers (about 124 KB per position at
  * the Qwen3-8B shape, plus 1.5 MB of gate/up rows) fit in the array with at

@@ -38,14 +38,13 @@
 #include <type_traits>
 
 #include "xp_internal.h"
+#include "xp_layer_plan.h"
 
 namespace xp {
 
 constexpr int kLinWaves = 8;        // k-split of k_linear
 constexpr int kLinMaxStream = 64;   // positions up to which the projections stream
-constexpr int kAttnWgs = 512;       // attention workgroups of a call at most (256 CUs x 2)
-constexpr int kHd = 128;            // head_dim (the only one built)
-constexpr int kSub = 64;            // keys per attention sub-chunk (one LDS stage)
+static_assert(kPlanTile == kTile, "position blocks");
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -271,7 +270,6 @@ __global__ __launch_bounds__(kLinWaves * kWave, 2) void k_linear(
 // ---------------------------------------------------------------------------
 constexpr int kGsWaves = 16;
 constexpr int kGsPF = 5;                // items in flight per wave
-constexpr int kGsXChunks = 512;         // 16-byte chunks of x per position (K <= 4096)
 
 __device__ __forceinline__ int gs_slot(int row, int c) { return row * 8 + (c ^ ((row & 7) ^ (row >> 3))); }
 
@@ -569,49 +567,11 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }
 
-// Waves of a workgroup: one per (query head of the group, position block),
-// times KH = 2 key halves where that leaves at most eight (the two waves of a
-// pair take keys 0..31 and 32..63 of every sub-chunk with their own running
-// maximum, sum and O, merged at the end), so that a CU holds enough waves to
-// hide each one's latency (with eight pairs the halves' extra registers cost
-// more than they hide: measured).
-__host__ __device__ constexpr int attn_halves(int grp, int npb) { return grp * npb <= 4 ? 2 : 1; }
-__host__ __device__ constexpr int attn_waves(int grp, int npb) {
-  return grp * npb * attn_halves(grp, npb);
-}
-// Ring stages (32 KB each) and workgroups per CU: two workgroups of two stages,
-// or one of three: with 16 waves, and with the eight of the key halves, whose
-// one head-block pair in flight per wave leaves HBM latency to the ring (batch
-// 32 x 16, 8192 keys: 538 us a forward with one workgroup and three stages, 556
-// with two and two, 542 with one and five; batch 64 x 32: 1520 and 1476).
-__host__ __device__ constexpr int attn_cu_wgs(int grp, int npb) {
-  return attn_waves(grp, npb) >= 16 || grp * npb == 4 ? 1 : 2;
-}
-// Waves per SIMD that the registers must allow for that.
-__host__ __device__ constexpr int attn_occ(int grp, int npb) {
+// Waves per SIMD that the registers must allow for attn_cu_wgs workgroups per CU.
+constexpr int attn_occ(int grp, int npb) {
   const int w = attn_waves(grp, npb) * attn_cu_wgs(grp, npb) / 4;
   return w < 1 ? 1 : w;
 }
-// The equal shares of a call's pre_all * nkv sub-chunks over W workgroups (W0 at
-// most, and no empty share): share w is [first(w), first(w + 1)).
-struct AttnShare {
-  int64_t T;
-  int W;
-  __device__ __forceinline__ AttnShare(int pre_all, int nkv, int W0)
-      : T((int64_t)pre_all * nkv), W(T < W0 ? (int)T : W0) {}
-  // (32-bit divisions where they do: 64-bit ones are a long chain at the start of
-  // every workgroup)
-  __device__ __forceinline__ int64_t first(int w) const {
-    return T < kSmall ? (int64_t)((uint32_t)T * (uint32_t)w / (uint32_t)W) : T * w / W;
-  }
-  // the share that holds sub-chunk f
-  __device__ __forceinline__ int of(int64_t f) const {
-    return T < kSmall ? (int)((((uint32_t)f + 1) * (uint32_t)W - 1) / (uint32_t)T)
-                      : (int)(((f + 1) * W - 1) / T);
-  }
-  static constexpr int64_t kSmall = (int64_t)1 << 22;   // times kAttnWgs stays below 2^32
-};
-
 template <int GRP, int NPB>
 struct AttnShape {
   static constexpr int KH = attn_halves(GRP, NPB);
@@ -743,7 +703,7 @@ __global__ __launch_bounds__(attn_waves(GRP, NPB) * kWave, attn_occ(GRP, NPB)) v
     const uint16_t* __restrict__ qn, const uint16_t* __restrict__ kcache,
     const uint16_t* __restrict__ vcache, const uint16_t* __restrict__ kb,
     const uint16_t* __restrict__ vb, const int32_t* __restrict__ ctx_len, int Cmax, int B,
-    int nh, int nkv, int causal, int batch, const int32_t* __restrict__ pre, int W0,
+    int nh, int nkv, int causal, int batch, const int32_t* __restrict__ pre, int W0, int ns,
     float* __restrict__ opart, float* __restrict__ mlpart) {
   using SH = AttnShape<GRP, NPB>;
   constexpr int W = SH::W, NS = SH::NS, KH = SH::KH;
@@ -761,31 +721,47 @@ __global__ __launch_bounds__(attn_waves(GRP, NPB) * kWave, attn_occ(GRP, NPB)) v
   const int hw = pair % GRP, pb = pair / GRP;
   const int t0 = kh * NT;                        // first tile of the wave's keys
   const int g = lane >> 4, li = lane & 15;
-  // this workgroup's share [f, f1) of the sub-chunks, and where it begins:
-  // KV head kvh of sequence b, sub-chunk jc of it
-  const AttnShare share(pre[batch], nkv, W0);
-  const int w = blockIdx.x;
-  int64_t f = share.first(w);
-  const int64_t f1 = share.first(w + 1);
-  if (w >= share.W || f >= f1) return;           // whole workgroup
-  int b = -1;
-  for (int b0 = 0; b0 < batch; b0 += kWave)
-    b += __popcll(__ballot(b0 + lane < batch &&
-                           (int64_t)pre[b0 + lane < batch ? b0 + lane : 0] * nkv <= f));
-  b = __builtin_amdgcn_readfirstlane(b);
-  int nb = pre[b + 1] - pre[b];
-  int kvh, jc;
-  {
+  // this workgroup's sub-chunks [f, f1), and where they begin: KV head kvh of
+  // sequence b, sub-chunk jc of it; its partials are pw + segment
+  int pw = blockIdx.x;
+  int64_t f, f1;
+  int b, kvh, jc;
+  int C, nb;                                     // context keys of sequence b, its sub-chunks
+  auto sequence = [&]() {
+    C = ctx_len[b];
+    C = C < 0 ? 0 : (C > Cmax ? Cmax : C);
+    nb = (C + B + kSub - 1) / kSub;
+  };
+  if (ns > 0) {                                  // a part of one segment
+    const int seg = pw / ns, i = pw - seg * ns;
+    b = seg / nkv;
+    kvh = seg - b * nkv;
+    sequence();
+    const AttnSegment parts(nb, ns);
+    if (i >= parts.n) return;                    // whole workgroup
+    jc = parts.first(i);
+    f = jc;
+    f1 = parts.first(i + 1);
+    pw -= seg;
+  } else {                                       // a share of all of them
+    const AttnShare share(pre[batch], nkv, W0);
+    f = share.first(pw);
+    f1 = share.first(pw + 1);
+    if (pw >= share.W || f >= f1) return;        // whole workgroup
+    b = -1;
+    for (int b0 = 0; b0 < batch; b0 += kWave)
+      b += __popcll(__ballot(b0 + lane < batch &&
+                             (int64_t)pre[b0 + lane < batch ? b0 + lane : 0] * nkv <= f));
+    b = __builtin_amdgcn_readfirstlane(b);
+    sequence();
     const uint32_t in = (uint32_t)(f - (int64_t)pre[b] * nkv);   // < nkv nb
     kvh = (int)(in / (uint32_t)nb);
     jc = (int)(in - (uint32_t)kvh * (uint32_t)nb);
   }
   for (;;) {
   const int nj = (int)(nb - jc < f1 - f ? nb - jc : f1 - f);   // sub-chunks of this part (>= 1)
-  int C = ctx_len[b];
-  C = C < 0 ? 0 : (C > Cmax ? Cmax : C);
   const int nkeys = C + B, kbase = jc * kSub;
-  const size_t pidx = (((size_t)w + (size_t)b * nkv + kvh) * NPB + pb) * GRP + hw;
+  const size_t pidx = (((size_t)pw + (size_t)b * nkv + kvh) * NPB + pb) * GRP + hw;
   float* op = opart + pidx * (kTile * kHd);
   float* ml = mlpart + pidx * (2 * kTile);
 
@@ -921,7 +897,7 @@ __global__ __launch_bounds__(attn_waves(GRP, NPB) * kWave, attn_occ(GRP, NPB)) v
   if (++kvh == nkv) {
     kvh = 0;
     ++b;
-    nb = pre[b + 1] - pre[b];
+    sequence();
   }
   __syncthreads();                               // every wave is done with the ring's LDS
   }
@@ -940,19 +916,29 @@ __global__ __launch_bounds__(256) void k_attn_comb(const float* __restrict__ opa
                                                    const float* __restrict__ mlpart, int M, int B,
                                                    int npb, int nkv, int batch,
                                                    const int32_t* __restrict__ pre, int W0,
-                                                   uint16_t* __restrict__ attn) {
+                                                   int ns0, uint16_t* __restrict__ attn) {
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
   constexpr int NH = GRP / HW;                   // waves of a KV head
   if (wv >= M * nkv * NH) return;                // whole wave
   const int m = wv / (nkv * NH), kh = wv - m * (nkv * NH), kvh = kh / NH, h0 = HW * (kh % NH);
   const int b = m / B, p = m - b * B, pb = p / kTile, q = p - pb * kTile;
-  // the segment's parts: shares wa .. wa + ns - 1, partial numbers share + segment
-  const AttnShare share(pre[batch], nkv, W0);
+  // the segment's parts, in order: partials pa .. pa + ns - 1 (k_attn's numbers)
   const int nb = pre[b + 1] - pre[b];
-  const int64_t fa = (int64_t)pre[b] * nkv + (int64_t)kvh * nb;
-  const int wa = share.of(fa), ns = share.of(fa + nb - 1) - wa + 1;
-  const size_t first = (((size_t)wa + (size_t)b * nkv + kvh) * npb + pb) * GRP + h0;
+  const int64_t seg = (int64_t)b * nkv + kvh;
+  int64_t pa;
+  int ns;
+  if (ns0 > 0) {
+    pa = seg * ns0;
+    ns = AttnSegment(nb, ns0).n;
+  } else {                                        // shares wa .. wa + ns - 1
+    const AttnShare share(pre[batch], nkv, W0);
+    const int64_t fa = (int64_t)pre[b] * nkv + (int64_t)kvh * nb;
+    const int wa = share.of(fa);
+    ns = share.of(fa + nb - 1) - wa + 1;
+    pa = wa + seg;
+  }
+  const size_t first = ((size_t)pa * npb + pb) * GRP + h0;
   const size_t step = (size_t)npb * GRP;
   auto mlv = [&](int s, int h, float& ms, float& ls) {
     const size_t pi = first + (size_t)(s < ns ? s : ns - 1) * step + h;
@@ -1077,8 +1063,7 @@ struct LayerBufs {
   size_t part_floats = 0;            // floats `part` holds
 };
 
-struct xp_layer {
-  int H, nh, nkv, ffn, grp;
+struct xp_layer : LayerDims {
   float eps, theta;
   const uint16_t *g_attn, *Wq, *Wk, *Wv, *g_q, *g_k, *Wo, *g_mlp, *Wg, *Wu, *Wd;
   int max_batch = 0, max_B = 0, max_ctx = 0;
@@ -1106,8 +1091,6 @@ static xp_status layer_fail(xp_layer* L, xp_status s, const char* fmt, ...) {
 extern "C" const char* xp_layer_last_error(const xp_layer* L) {
   return L ? L->err.c_str() : g_layer_err.c_str();
 }
-
-static int attn_chunks(int C_max, int B, int keys) { return (C_max + B + keys - 1) / keys; }
 
 // Checks the weight set and copies it into *L (shapes and pointers only).
 // Errors are reported through layer_fail(nullptr, ...).
@@ -1159,13 +1142,6 @@ static bool rows_fit_int32(const xp_layer& L, int64_t positions) {
   return positions * widest < ((int64_t)1 << 31);
 }
 
-// The gate/up projections write fp32 [M][2 F] to GU on the stream kernel's
-// path only (calls of at most one 16-position block, H within its LDS copy of
-// x); the tiled GEMM and k_linear form the SwiGLU product themselves.
-static size_t gu_rows_for(const xp_layer& L, size_t Mx) {
-  return (size_t)L.H <= 8 * (size_t)kGsXChunks ? std::min(Mx, (size_t)kTile) : 0;
-}
-
 // Split-K slabs are used by the tiled GEMM only (calls above kLinMaxStream
 // positions); their size is bounded independently of M.
 static size_t part_floats_for(size_t Mx) {
@@ -1177,49 +1153,22 @@ static size_t part_floats_for(size_t Mx) {
 // base == nullptr only the size is computed.
 static size_t carve(const xp_layer& L, size_t Mx, size_t nparts, size_t gu_rows,
                     size_t part_floats, char* base, LayerBufs* b) {
-  const size_t H = L.H, nhd = (size_t)L.nh * kHd, kvd = (size_t)L.nkv * kHd, F = L.ffn;
   LayerBufs t;
   t.nparts = nparts;
   t.gu_rows = gu_rows;
   t.part_floats = part_floats;
-  struct Slice {
-    void** p;
-    size_t bytes;
-  } sl[] = {
-      {(void**)&t.x32, Mx * H * 4},           {(void**)&t.u, Mx * H * 2},
-      {(void**)&t.qkv, Mx * (nhd + 2 * kvd) * 4}, {(void**)&t.qn, Mx * nhd * 2},
-      {(void**)&t.kb, Mx * kvd * 2},          {(void**)&t.vb, Mx * kvd * 2},
-      {(void**)&t.opart, nparts * kTile * kHd * 4}, {(void**)&t.mlpart, nparts * 2 * kTile * 4},
-      {(void**)&t.attn, Mx * nhd * 2},        {(void**)&t.x1, Mx * H * 4},
-      {(void**)&t.act, Mx * F * 2},           {(void**)&t.h32, Mx * H * 4},
-      {(void**)&t.GU, (gu_rows ? gu_rows : 1) * 2 * F * 4},
-      {(void**)&t.part, (part_floats ? part_floats : 1) * 4},
-  };
+  const std::array<size_t, 14> bytes = layer_sizes(L, Mx, nparts, gu_rows, part_floats);
+  void** at[] = {(void**)&t.x32,    (void**)&t.u,    (void**)&t.qkv, (void**)&t.qn,  (void**)&t.kb,
+                 (void**)&t.vb,     (void**)&t.opart, (void**)&t.mlpart, (void**)&t.attn,
+                 (void**)&t.x1,     (void**)&t.act,  (void**)&t.h32, (void**)&t.GU,  (void**)&t.part};
   size_t off = 0;
-  for (auto& q : sl) {
-    if (base) *q.p = base + off;
-    off += (q.bytes + 255) / 256 * 256;
+  for (size_t i = 0; i < bytes.size(); ++i) {
+    if (base) *at[i] = base + off;
+    off += layer_slice(bytes[i]);
   }
   if (part_floats == 0) t.part = nullptr;
   if (base && b) *b = t;
   return off;
-}
-
-// Attention shares of one call: W workgroups (at most one per 64-key sub-chunk
-// that the call could have), and the partials they write at most: (W + batch
-// nkv - 1) npb grp.
-struct AttnPlan {
-  int W;
-  size_t parts;
-};
-static AttnPlan attn_plan(const xp_layer& L, int batch, int B, int W) {
-  const size_t npb = (B + kTile - 1) / kTile;
-  return {W, ((size_t)W + (size_t)batch * L.nkv - 1) * npb * L.grp};
-}
-static AttnPlan attn_plan_default(const xp_layer& L, int batch, int B, int C_max) {
-  const size_t w64 = (size_t)batch * L.nkv * attn_chunks(C_max, B, kSub);
-  const int wgs = kAttnWgs / 2 * attn_cu_wgs(L.grp, (B + kTile - 1) / kTile);
-  return attn_plan(L, batch, B, (int)std::min(w64, (size_t)wgs));
 }
 
 extern "C" xp_status xp_layer_create(const xp_layer_weights* w, int32_t max_batch, int32_t max_B,
@@ -1245,9 +1194,7 @@ extern "C" xp_status xp_layer_create(const xp_layer_weights* w, int32_t max_batc
   L->max_B = max_B;
   L->max_ctx = max_ctx;
   const size_t Mx = (size_t)max_batch * max_B;
-  // attention partials (attn_plan): any call has at most these
-  const size_t qmax = (size_t)max_batch * L->nkv, npbmax = (max_B + kTile - 1) / kTile;
-  const size_t nparts = (kAttnWgs + qmax) * npbmax * L->grp;
+  const size_t nparts = attn_parts_max(*L, max_batch, max_B);
   const size_t gu = gu_rows_for(*L, Mx), pf = part_floats_for(Mx);
   const size_t total = carve(*L, Mx, nparts, gu, pf, nullptr, nullptr);
   const hipError_t e = hipMalloc(&L->ws, total);
@@ -1413,7 +1360,8 @@ static xp_status forward(const xp_layer& L, const LayerBufs& b, const AttnPlan& 
   hipLaunchKernelGGL((k_attn<GG, PB>), dim3(ap.W),                                            \
                      dim3(attn_waves(GG, PB) * kWave), 0, st,                                 \
                      b.qn, (const uint16_t*)k_cache, (const uint16_t*)v_cache, b.kb, b.vb,    \
-                     ctx_len, C_max, B, nh, nkv, causal, batch, pre, ap.W, b.opart, b.mlpart)
+                     ctx_len, C_max, B, nh, nkv, causal, batch, pre, ap.W, ap.ns, b.opart,    \
+                     b.mlpart)
   if (npb == 1) {
     if (grp == 1) XP_STEP("attention", XP_ATTN(1, 1));
     else if (grp == 2) XP_STEP("attention", XP_ATTN(2, 1));
@@ -1429,7 +1377,7 @@ static xp_status forward(const xp_layer& L, const LayerBufs& b, const AttnPlan& 
   // whole groups from 1024 waves on
 #define XP_COMB1(GG, HH)                                                                     \
   hipLaunchKernelGGL((k_attn_comb<GG, HH>), dim3((M * nkv * (GG / HH) + 3) / 4), dim3(256), 0, \
-                     st, b.opart, b.mlpart, M, B, npb, nkv, batch, pre, ap.W, b.attn)
+                     st, b.opart, b.mlpart, M, B, npb, nkv, batch, pre, ap.W, ap.ns, b.attn)
 #define XP_COMB(GG)                                                                          \
   do {                                                                                       \
     if (M * nkv >= 1024) XP_STEP("attention combine", XP_COMB1(GG, GG));                      \
@@ -1493,7 +1441,6 @@ extern "C" xp_status xp_layer_forward(xp_layer* L, int32_t batch, int32_t B, int
 // device address is looked up once per device with hipGetSymbolAddress and
 // kept in g_scratch.
 // ---------------------------------------------------------------------------
-constexpr size_t kScratchBytes = (size_t)64 << 20;
 constexpr int kMaxDevices = 64;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -1532,26 +1479,19 @@ extern "C" xp_status xp_layer_forward_noalloc(const xp_layer_weights* w, int32_t
   const size_t M = (size_t)batch * B;
   if (!rows_fit_int32(L, (int64_t)M))
     return layer_fail(nullptr, XP_EINVAL, "batch*B*max(H, heads*128, ffn) reaches 2^31");
-  // The buffers the call needs, its partials at the default number of shares;
-  // if those do not fit, fewer and longer shares.
-  const size_t gu = gu_rows_for(L, M);
-  const size_t fixed = carve(L, M, 0, gu, 0, nullptr, nullptr);
-  const size_t per_part = (size_t)kTile * kHd * 4 + (size_t)2 * kTile * 4;   // opart + mlpart
-  if (fixed + 2 * 256 + per_part > kScratchBytes)
+  // The buffers the call needs, its partials as the default plan cuts the work or,
+  // where those do not fit, as attn_plan_fit does.
+  const size_t gu = gu_rows_for(L, M), max_parts = scratch_parts(L, M);
+  if (max_parts == 0)
     return layer_fail(nullptr, XP_EINVAL,
-                      "%zu positions need %zu bytes of buffers; the static scratch holds %zu",
-                      M, fixed + per_part, kScratchBytes);
-  const size_t max_parts = (kScratchBytes - fixed - 2 * 256) / per_part;
-  AttnPlan ap = attn_plan_default(L, batch, B, C_max);
-  if (ap.parts > max_parts) {                    // as many shares as the partials allow
-    const size_t fit = max_parts / (((size_t)B + kTile - 1) / kTile * L.grp);   // W + segments - 1
-    const size_t segs = (size_t)batch * L.nkv;
-    if (fit < segs)
-      return layer_fail(nullptr, XP_EINVAL,
-                        "%d sequences x %d KV heads need more attention partials than the static "
-                        "scratch holds beside %zu positions", batch, L.nkv, M);
-    ap = attn_plan(L, batch, B, (int)(fit - segs + 1));
-  }
+                      "%zu positions need %zu bytes of buffers and attention partials; the static "
+                      "scratch holds %zu",
+                      M, carve(L, M, 1, gu, 0, nullptr, nullptr), kScratchBytes);
+  const AttnPlan ap = attn_plan_fit(L, batch, B, C_max, max_parts);
+  if (ap.W == 0)
+    return layer_fail(nullptr, XP_EINVAL,
+                      "%d sequences x %d KV heads need more attention partials than the static "
+                      "scratch holds beside %zu positions", batch, L.nkv, M);
   char* base = nullptr;
   const hipError_t e = scratch_ptr(&base);
   if (e != hipSuccess)

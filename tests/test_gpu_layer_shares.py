@@ -2,7 +2,7 @@
 MI355X): calls whose work list is shorter than the workgroups, one sequence cut
 into many parts, many short sequences in one share, shares that end inside the
 block's own keys, every group size and both block widths, and the static-scratch
-forward at its limit of partials."""
+forward where its partials do not fit."""
 import numpy as np
 import pytest
 
@@ -57,25 +57,36 @@ def test_attention_shares(nkv, grp, B, ctx, causal):
     assert np.abs(h[some] - ref).max() <= max(2e-2, 2.0 ** -8 * np.abs(ref).max())
 
 
-def test_static_scratch_with_fewer_shares():
-    """65 positions: the partials of the default shares do not fit beside the
-    buffers of the Qwen3-8B shape at this many KV heads, so fewer shares serve."""
+# more partials than the static scratch holds beside the buffers: fewer shares, one
+# part per KV head of a sequence, two parts
+@pytest.mark.parametrize("batch,c_max,ns", [(17, 400, 0), (22, 400, 1), (16, 2200, 2)])
+def test_static_scratch_without_room_for_the_default(batch, c_max, ns):
     import torch
+    from _layer_plan import plans
     from paper_2608_02438_amd.xpress import device_tensor, layer_forward_noalloc, \
         layer_weights_struct
-    w = synth.scaled(synth.configs.QWEN_B1, index=990, H=256, B=32, batch=8, n_heads=32,
-                     n_kv_heads=4, ffn=256, ctx_len=None, ctx_len_range=None)
-    print("static scratch, 8 x 32 positions, 32 heads", flush=True)
+    H, nh, nkv, ffn, B = 256, 64, 8, 256, 17
+    plan = plans([(H, nh, nkv, ffn, batch, B, c_max)])[0]
+    assert plan.parts > plan.room >= plan.fit_parts and plan.fit_ns == ns
+    print(f"static scratch, {batch} x {B} positions, {nh}/{nkv} heads: {plan}", flush=True)
+    w = synth.scaled(synth.configs.QWEN_B1, index=990 + ns, H=H, B=B, batch=batch, n_heads=nh,
+                     n_kv_heads=nkv, ffn=ffn, ctx_len=None, ctx_len_range=None)
     weights = synth.make_layer_weights(w)
-    inp = synth.make_layer_inputs(w, c_max=3000)
-    inp.ctx_len = np.array([3000, 0, 64, 2999, 1, 700, 128, 1500], dtype=np.int32)
+    inp = synth.make_layer_inputs(w, c_max=c_max)
+    inp.ctx_len = np.array([[c_max, 0, 64, c_max - 1, 1, 300, 128, 47][b % 8]
+                            for b in range(batch)], dtype=np.int32)
     dw = {k: device_tensor(weights[k]) for k in LAYER_WEIGHT_NAMES}
-    st = layer_weights_struct(dw, w.H, 32, 4, w.ffn)
-    h32 = torch.empty((8, 32, 256), dtype=torch.float32, device="cuda")
-    hb = torch.empty((8, 32, 256), dtype=torch.bfloat16, device="cuda")
-    layer_forward_noalloc(st, *[device_tensor(a) for a in (inp.x, inp.k_cache, inp.v_cache,
-                                                           inp.ctx_len)], h32, hb)
-    LP = O.layer_ref.LayerParams.from_arrays(weights, 32, 4, 128)
-    ref = O.layer_ref.layer_forward(LP, inp.x, inp.k_cache, inp.v_cache, inp.ctx_len)
+    st = layer_weights_struct(dw, H, nh, nkv, ffn)
+    args = [device_tensor(a) for a in (inp.x, inp.k_cache, inp.v_cache, inp.ctx_len)]
+    h32 = torch.full((batch, B, H), float("nan"), dtype=torch.float32, device="cuda")
+    hb = torch.empty((batch, B, H), dtype=torch.bfloat16, device="cuda")
+    layer_forward_noalloc(st, *args, h32, hb)
     got = h32.cpu().numpy()
-    assert np.abs(got - ref).max() <= max(2e-2, 2.0 ** -8 * np.abs(ref).max())
+    layer_forward_noalloc(st, *args, h32, hb)
+    assert np.array_equal(got.view(np.uint32), h32.cpu().numpy().view(np.uint32))
+    some = [0, 1, 2, 3, 4, batch - 1]
+    LP = O.layer_ref.LayerParams.from_arrays(weights, nh, nkv, 128)
+    ref = O.layer_ref.layer_forward(LP, inp.x[some], inp.k_cache[some], inp.v_cache[some],
+                                    inp.ctx_len[some])
+    assert np.isfinite(got).all()
+    assert np.abs(got[some] - ref).max() <= max(2e-2, 2.0 ** -8 * np.abs(ref).max())

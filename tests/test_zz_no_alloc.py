@@ -1,14 +1,15 @@
 """The allocation-free context-layer forward (xp_layer_forward_noalloc) on the
 device, through the C ABI: its output must match the handle-based
-xp_layer_forward on the same inputs (bit for bit where both take the same
-attention chunking; to the bf16 tolerance 2e-2 where the static scratch makes
-it read the context in longer chunks), on consecutive calls whose second one
-is smaller, and the oracle within the same tolerance."""
+xp_layer_forward on the same inputs (bit for bit where both cut the attention
+alike; to the bf16 tolerance 2e-2 where the static scratch has no room for that
+many partials), on consecutive calls whose second one is smaller, and the oracle
+within the same tolerance."""
 import numpy as np
 import pytest
 
 import oracle as O
 import synth
+from _layer_plan import plans
 from synth.configs import QWEN_B1
 
 pytestmark = pytest.mark.gpu
@@ -58,15 +59,19 @@ def _oracle(w, weights, inp):
 def test_noalloc_forward_matches_the_handle_forward_on_consecutive_calls():
     cases = [
         # (H, heads, kv, ffn, B, batch, ctx, exact): the first call, a smaller
-        # second one, then one whose default attention partials (8448 of
-        # 8.3 KB) exceed the scratch, so it reads the context in longer chunks
+        # second one, one of 64 positions with more than half of the scratch's
+        # partials, then one whose partials exceed the scratch (7672 of 8.3 KB
+        # where 7479 fit), so it reads the contexts in fewer parts
         (512, 8, 2, 768, 16, 3, [600, 3, 256], True),
         (256, 4, 2, 256, 8, 1, [50], True),
-        (512, 64, 8, 512, 16, 4, [4096, 4000, 1, 2500], False),
+        (512, 64, 8, 512, 16, 4, [4096, 4000, 1, 2500], True),
+        (512, 64, 8, 512, 1, 56, [200, 0, 1, 150, 199, 64, 65] * 8, False),
     ]
     for i, (H, nh, nkv, ffn, B, batch, ctx, exact) in enumerate(cases):
         _say(f"case {i}: noalloc layer H={H} heads={nh}/{nkv} ffn={ffn} B={B} batch={batch} "
              f"ctx={ctx}")
+        plan = plans([(H, nh, nkv, ffn, batch, B, max(ctx))])[0]
+        assert (plan.parts <= plan.room) == exact
         w, weights, inp = _case(H, nh, nkv, ffn, B, batch, ctx, index=990 + i)
         r32, rb, n32, nb = _both(w, weights, inp)
         assert np.all(np.isfinite(n32))
