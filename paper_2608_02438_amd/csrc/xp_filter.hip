@@ -304,8 +304,9 @@ __device__ void select_mass(XF x, int n, TF tok, float p, FState& s, FShared& sh
 // The tokens of key >= thr in vocabulary order, into sh.ck / sh.cv: only the
 // units (unit_lo(u) .. unit_lo(u + 1), u < U <= kUnitsMax) whose maximum
 // reaches thr are read, a wave per unit: once to count, once to place.
-// Returns their number, or -1 when a list would overflow.  um[j] is the
-// maximum of unit (kUnitsMax / kFThreads) threadIdx.x + j.
+// Returns their number, or -1 when a list would overflow or none reaches thr (a
+// row with NaN: the maxima pass over it, a key does not).  um[j] is the maximum
+// of unit (kUnitsMax / kFThreads) threadIdx.x + j.
 constexpr int kUPT = kUnitsMax / kFThreads;
 template <class XF, class UF>
 __device__ int collect(XF x, int V, int U, UF unit_lo, const float (&um)[kUPT], uint32_t thr,
@@ -351,7 +352,7 @@ __device__ int collect(XF x, int V, int U, UF unit_lo, const float (&um)[kUPT], 
   }
   int n;
   int off = block_scan(sum, &n, sh);
-  if (n > kCand) return -1;
+  if (n > kCand || n == 0) return -1;
   // each unit's first place goes where its entry of the unit list was read from
   int place[UPT];
 #pragma unroll

@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from _parity import custom_problem, make_refiner, run_device, upload
-from test_gpu_filter import _check
+from test_gpu_filter import _check, _verify
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +43,28 @@ def test_ties_overflow(V, k, p):
                           top_k=k, top_p=p)
     ref, dev = make_refiner(prob), upload(prob)
     _check(prob, ref, dev, max_excused=0)
+
+
+# a NaN beside the row's largest logit, a row of NaN (of the sign that sorts below
+# every number), more NaN than top-k keeps on the general way: no token has mass and
+# the choice is the first of the vocabulary, as the general way makes it; the last
+# sequence has none of them and keeps its token
+def test_target_rows_with_nan():
+    import torch
+    print("target rows with NaN, V=5004 k=[1, 4, 2000, 50]", flush=True)
+    prob = custom_problem("bf16", H=256, V=5004, B=4, batch=4, K=2, sigmas=STRESS,
+                          temp="sample", seed=95, top_k=[1, 4, 2000, 50], top_p=1.0)
+    ref, dev = make_refiner(prob), upload(prob)
+    run = run_device(ref, prob, dev)
+    target_ids = prob.inp.target_ids(run.ids)
+    n0, nx0 = _verify(ref, prob, run, dev, target_ids)
+    tl = prob.inp.target_logits.copy()
+    for k in range(prob.B + 1):
+        tl[0, k, tl[0, k].argmax() ^ 1] = np.nan
+    tl[1] = np.array([0xFFC00000], dtype=np.uint32).view(np.float32)[0]
+    tl[2, :, :2500] = np.nan
+    dev["target_logits"] = torch.from_numpy(tl).cuda()
+    n, nx = _verify(ref, prob, run, dev, target_ids)
+    print(f"  n={n.tolist()} next={nx.tolist()}", flush=True)
+    assert n[:3].tolist() == [0, 0, 0] and nx[:3].tolist() == [0, 0, 0]
+    assert (n[3], nx[3]) == (n0[3], nx0[3])
