@@ -468,9 +468,11 @@ __global__ __launch_bounds__(256) void k_qkrope(
   int C = ctx_len[m / B];
   C = C < 0 ? 0 : (C > Cmax ? Cmax : C);
   // the angle in half turns, pos theta^(-2 l / hd) / pi, and its sine and cosine
-  // in double (exp2 and sincospi cost a third of pow, sin and cos)
+  // in double (exp2 and sincospi cost a third of pow, sin and cos); theta^0 is 1
+  // for every theta, an infinite one too (where 0 lt is not a number)
   const double pos = (double)(C + m % B);
-  const double half = pos * (exp2(-2.0 * (double)lane / (double)kHd * lt) * 0.31830988618379067154);
+  const double inv = lane == 0 ? 1.0 : exp2(-2.0 * (double)lane / (double)kHd * lt);
+  const double half = pos * (inv * 0.31830988618379067154);
   double sd, cd;
   sincospi(half, &sd, &cd);
   const float cs = (float)cd, sn = (float)sd;

@@ -96,6 +96,25 @@ def test_layer_matches_oracle(H, nh, nkv, ffn, B, batch, ctx, causal):
     layer.close()
 
 
+@pytest.mark.parametrize("theta", [float("inf"), 0.5])
+def test_rope_base_at_its_ends(theta):
+    """An infinite base turns frequency 0 alone; one below 1 speeds up with the
+    frequency."""
+    _say(f"case: rope_theta={theta}")
+    from paper_2608_02438_amd.xpress import LAYER_WEIGHT_NAMES, Layer, device_tensor
+    w, weights, inp = _case(256, 4, 2, 256, 8, 2, [70, 3], index=845)
+    dw = {n: device_tensor(weights[n]) for n in LAYER_WEIGHT_NAMES}
+    layer = Layer(dw, w.H, w.n_heads, w.n_kv_heads, w.ffn, max_batch=2, max_B=8, max_ctx=70,
+                  theta=theta)
+    h32, _ = layer.forward(*[device_tensor(a) for a in (inp.x, inp.k_cache, inp.v_cache,
+                                                        inp.ctx_len)])
+    P = O.layer_ref.LayerParams.from_arrays(weights, w.n_heads, w.n_kv_heads, w.head_dim,
+                                            theta=theta)
+    ref = O.layer_ref.layer_forward(P, inp.x, inp.k_cache, inp.v_cache, inp.ctx_len, True)
+    assert np.abs(h32.cpu().numpy() - ref).max() <= max(ATOL, 2.0 ** -8 * np.abs(ref).max())
+    layer.close()
+
+
 def test_layer_large_call_takes_128_key_chunks():
     """8 sequences x 8 KV heads x up to 33 chunks of 128 keys: at least 512
     workgroups, so the forward takes the 128-key attention chunks (smaller
