@@ -9,6 +9,7 @@
 
 #include "../../include/xpress.h"
 #include "xp_device.h"
+#include "xp_layer_plan.h"
 
 namespace xp {
 
@@ -126,16 +127,11 @@ hipError_t launch_rspace(xp_handle* h, int batch, int pass, uint32_t flags, cons
                          hipStream_t st);
 bool pass_fused_ok(const xp_handle* h, int batch, const uint8_t* temp);
 int gemm_units(const xp_handle* h, int M);
-// the context layer's projections for many positions (xp_lgemm.hip): tile
-// size bn (128 or 256; 0: no plan) and S k splits; with S > 1 the launch
-// writes S slabs of [M][N] fp32 partial products (Y, with R = Yb = NULL);
-// the gate/up projections form the SwiGLU product (S = 1)
-constexpr int kLayerSplitMax = 8;
+// the context layer's projections for many positions (xp_lgemm.hip), on a plan
+// of layer_plan; with S > 1 the launch writes S slabs of [M][N] fp32 partial
+// products (Y, with R = Yb = NULL); the gate/up projections form the SwiGLU
+// product (S = 1)
 constexpr size_t kLayerPartFloats = (size_t)16 << 20;   // slab values a layer holds (64 MB)
-struct LayerPlan {
-  int bn, S;
-};
-LayerPlan layer_plan(int n0, int n1, int N, int K, int M, bool glu, size_t part_floats);
 hipError_t launch_layer_gemm(LayerPlan pl, const uint16_t* W0, const uint16_t* W1,
                              const uint16_t* W2, int n0, int n1, int N, int K, const uint16_t* X,
                              int M, const float* R, int ldr, float* Y, uint16_t* Yb, int ldy,

@@ -168,4 +168,59 @@ inline size_t scratch_parts(const LayerDims& L, size_t M) {
   return fixed < kScratchBytes ? (kScratchBytes - fixed) / per : 0;
 }
 
+// ---------------------------------------------------------------------------
+// A projection of more than 64 positions on the tiled GEMM: bn x bn tiles (128 or
+// 256; 0: no plan) and S parts of k.
+struct LayerPlan {
+  int bn, S;
+};
+constexpr int kLayerSplitMax = 8;
+constexpr int kGemmWgs = 256;       // workgroups of the persistent grid (8 XCDs x 32)
+// k of a stage of the pipeline, the least that a part of k differs by
+constexpr int gemm_stage_k(int bn) { return bn == 128 ? 64 : 32; }
+// The first of the nk stages in part s of S (s = S: nk): the parts are equal, or
+// a stage apart where S does not divide nk.
+constexpr int split_first(int nk, int S, int s) { return s * nk / S; }
+// Unequal parts need S to divide 8: a workgroup's tiles lie 8 apart and are then
+// all of one part, so that one stage count serves them.  (K is a multiple of 256,
+// so only S = 8 on 128 x 128 tiles needs unequal parts, at odd multiples.  Equal
+// parts alone leave it S = 4: ffn 11008, 80 and 128 positions, 151 and 168 us a
+// forward, 144 and 161 with unequal ones.)
+constexpr bool split_ok(int nk, int S) { return nk % S == 0 || 8 % S == 0; }
+// Tile size and parts of k of one projection: among 128 x 128 and 256 x 256
+// tiles (bn dividing every stacked weight's rows) and S = 1 .. kLayerSplitMax
+// (at least 512 k in every part, S M N fp32 slab values within part_floats; GLU:
+// S = 1), the one with the least estimated time: rounds of one work item per
+// workgroup of the persistent grid, an item costing 17 us plus its flops (the
+// longest part's) at 3.6 TFLOP/s per CU on 128 x 128 tiles or 4.3 on 256 x 256
+// (fitted to the launches of the Qwen3-8B projections at 128 to 2048 positions
+// with 32 k a stage on both), plus one read of the slabs at 5 TB/s by the kernel
+// that adds them.
+inline LayerPlan layer_plan(int n0, int n1, int N, int K, int M, bool glu, size_t part_floats) {
+  LayerPlan best{0, 1};
+  if (M < 1) return best;
+  double tbest = 0.0;
+  for (int bn = 128; bn <= 256; bn *= 2) {
+    if (N % bn != 0 || n0 % bn != 0 || n1 % bn != 0) continue;
+    const int gk = gemm_stage_k(bn), nk = K / gk;
+    if (K % gk != 0) continue;
+    const double rate = bn == 128 ? 3.6e12 : 4.3e12;
+    const long tiles = (long)(N / bn) * ((M + bn - 1) / bn);
+    for (int S = 1; S <= (glu ? 1 : kLayerSplitMax); ++S) {
+      if (!split_ok(nk, S) || (S > 1 && nk / S < 512 / gk)) continue;
+      if (S > 1 && (double)S * M * N > (double)part_floats) continue;
+      const long items = tiles * S;
+      const double rounds = (double)((items + kGemmWgs - 1) / kGemmWgs);
+      const int longest = (nk + S - 1) / S * gk;
+      double t = rounds * (17e-6 + 2.0 * bn * bn * (double)longest / rate);
+      if (S > 1) t += 4.0 * S * (double)M * N / 5e12;
+      if (best.bn == 0 || t < tbest) {
+        best = LayerPlan{bn, S};
+        tbest = t;
+      }
+    }
+  }
+  return best;
+}
+
 }  // namespace xp

@@ -1,10 +1,10 @@
 // The context layer's projections for many positions on the tiled bf16 GEMM
 // pipeline of xp_gemm_pipe.h (the LM-head GEMM's), in three forms:
 //   plain    y = X W^T (+ residual), fp32 and/or bf16;
-//   split-K  the k range cut into S equal parts, each tile writing its fp32
-//            partial product to slab s of [S][M][N]; the kernel that reads
-//            y next adds the slabs in slab order (so the result does not
-//            depend on timing);
+//   split-K  the k range cut into S parts (equal, or a stage apart), each tile
+//            writing its fp32 partial product to slab s of [S][M][N]; the
+//            kernel that reads y next adds the slabs in slab order (so the
+//            result does not depend on timing);
 //   GLU      bf16(silu(X Wg^T) * (X Wu^T)): a tile's rows are gate and up
 //            rows of the same features, so the product is formed in the
 //            epilogue.
@@ -23,8 +23,12 @@
 
 namespace xp {
 
+static_assert(GemmShape<128, 128>::GK == gemm_stage_k(128) &&
+                  GemmShape<256, 256>::GK == gemm_stage_k(256) && kGemmWgs == 8 * kGPerXcd,
+              "the plan's figures");
 
-// Rows of tile ti (virtual row tile v = sc.tile(ti) = rt S + s, k from s kt).
+// Rows of tile ti (virtual row tile v = sc.tile(ti) = rt S + s, k from part s's
+// first of the nk stages).
 // Plain: BN consecutive rows of whichever of W0 | W1 | W2 holds stacked row
 // rt BN.  GLU: the features f0 = rt BN / 2 .. + BN / 2 of the gate (W0) and up
 // (W1) weights; in each wave's half of the tile the first half of the 32-row
@@ -32,13 +36,13 @@ namespace xp {
 template <int BN, bool GLU>
 struct LayerRows {
   const uint16_t *W0, *W1, *W2;
-  int n0, n1, K, S, kt;
+  int n0, n1, K, S, nk;
   const GemmSched* sc;
   const uint16_t *w = nullptr, *wu = nullptr;
   int xk = 0;
   __device__ void prep(int ti) {
     const int v = sc->tile(ti), rt = v / S, s = v - rt * S;
-    xk = s * kt;
+    xk = split_first(nk, S, s) * GemmShape<BN, BN>::GK;
     if constexpr (GLU) {
       const size_t f0 = (size_t)rt * (BN / 2);
       w = W0 + f0 * K + xk;
@@ -134,7 +138,9 @@ struct LayerEpi {
   }
 };
 
-// N stacked rows (GLU: 2F, gate and up), S k splits of K / S each.
+// N stacked rows (GLU: 2F, gate and up), S parts of k.  A workgroup's tiles have
+// parts of one length: where the lengths differ S divides 8 (split_ok), and the
+// tiles, 8 apart, are all of one part.
 template <int BN, int BM, bool GLU>
 __global__ __launch_bounds__(kGWaves * kWave) void k_layer_gemm(
     const uint16_t* __restrict__ W0, const uint16_t* __restrict__ W1,
@@ -145,47 +151,12 @@ __global__ __launch_bounds__(kGWaves * kWave) void k_layer_gemm(
   const GemmSched sc(nMb, gpx);
   const int ntl = sc.count(N / BN * S);
   if (ntl == 0) return;                                            // whole workgroup
-  const int p0 = sc.mb * BM, kt = K / S;
-  LayerRows<BN, GLU> rows{W0, W1, W2, n0, n1, K, S, kt, &sc};
+  constexpr int GK = GemmShape<BN, BM>::GK;
+  const int p0 = sc.mb * BM, nk = K / GK, s0 = sc.tile(0) % S;
+  const int kt = (split_first(nk, S, s0 + 1) - split_first(nk, S, s0)) * GK;
+  LayerRows<BN, GLU> rows{W0, W1, W2, n0, n1, K, S, nk, &sc};
   LayerEpi<BN, BM, GLU> epi{&sc, R, Y, Yb, M, ldr, ldy, p0, S, slab};
   gemm_tiles<BN, BM>(rows, epi, X, K, M, kt, ntl, p0, lds);
-}
-
-// Tile size and k splits of one projection: among 128 x 128 and 256 x 256
-// tiles (BN dividing every stacked weight's rows) and S = 1 .. kLayerSplitMax
-// splits (S dividing the stages of 64 or 32 k, at least 512 k per split, S M N fp32
-// slab values within part_floats; GLU: S = 1), the one with the least
-// estimated time: rounds of one work item per workgroup of the persistent
-// grid, an item costing 17 us plus its flops at 3.6 TFLOP/s per CU on 128 x
-// 128 tiles or 4.3 on 256 x 256 (fitted to the measured launches of the
-// Qwen3-8B projections at 128 to 2048 positions), plus one read of the slabs
-// at 5 TB/s by the kernel that adds them.  bn = 0: no plan (K not a multiple
-// of the stage or no tile divides the rows).
-LayerPlan layer_plan(int n0, int n1, int N, int K, int M, bool glu, size_t part_floats) {
-  LayerPlan best{0, 1};
-  if (M < 1) return best;
-  const int slots = 8 * kGPerXcd;
-  double tbest = 0.0;
-  for (int bn = 128; bn <= 256; bn *= 2) {
-    if (N % bn != 0 || n0 % bn != 0 || n1 % bn != 0) continue;
-    const int gk = bn == 128 ? 64 : 32, nk = K / gk;    // k per stage, stages
-    if (K % gk != 0) continue;
-    const double rate = bn == 128 ? 3.6e12 : 4.3e12;
-    const long tiles = (long)(N / bn) * ((M + bn - 1) / bn);
-    for (int S = 1; S <= (glu ? 1 : kLayerSplitMax); ++S) {
-      if (nk % S != 0 || (S > 1 && nk / S < 512 / gk)) continue;
-      if (S > 1 && (double)S * M * N > (double)part_floats) continue;
-      const long items = tiles * S;
-      const double rounds = (double)((items + slots - 1) / slots);
-      double t = rounds * (17e-6 + 2.0 * bn * bn * (double)(K / S) / rate);
-      if (S > 1) t += 4.0 * S * (double)M * N / 5e12;
-      if (best.bn == 0 || t < tbest) {
-        best = LayerPlan{bn, S};
-        tbest = t;
-      }
-    }
-  }
-  return best;
 }
 
 template <bool GLU>
@@ -209,8 +180,9 @@ hipError_t launch_layer_gemm(LayerPlan pl, const uint16_t* W0, const uint16_t* W
                              const uint16_t* W2, int n0, int n1, int N, int K, const uint16_t* X,
                              int M, const float* R, int ldr, float* Y, uint16_t* Yb, int ldy,
                              hipStream_t st) {
-  if ((pl.bn != 128 && pl.bn != 256) || pl.S < 1 ||
-      K % (pl.S * (pl.bn == 128 ? 64 : 32)) != 0 || N % pl.bn != 0 || n0 % pl.bn != 0 || n1 % pl.bn != 0 || (pl.S > 1 && (R || Yb || !Y || ldy != N)))
+  if ((pl.bn != 128 && pl.bn != 256) || pl.S < 1 || K % gemm_stage_k(pl.bn) != 0 ||
+      !split_ok(K / gemm_stage_k(pl.bn), pl.S) || N % pl.bn != 0 || n0 % pl.bn != 0 ||
+      n1 % pl.bn != 0 || (pl.S > 1 && (R || Yb || !Y || ldy != N)))
     return hipErrorInvalidValue;
   launch<false>(pl, W0, W1, W2, n0, n1, N, K, X, M, R, ldr, Y, Yb, ldy, st);
   return hipGetLastError();
@@ -218,7 +190,7 @@ hipError_t launch_layer_gemm(LayerPlan pl, const uint16_t* W0, const uint16_t* W
 
 hipError_t launch_layer_glu(LayerPlan pl, const uint16_t* Wg, const uint16_t* Wu, int F, int K,
                             const uint16_t* X, int M, uint16_t* act, int ldy, hipStream_t st) {
-  if ((pl.bn != 128 && pl.bn != 256) || pl.S != 1 || K % 64 != 0 || (2 * F) % pl.bn != 0 ||
+  if ((pl.bn != 128 && pl.bn != 256) || pl.S != 1 || K % gemm_stage_k(pl.bn) != 0 || (2 * F) % pl.bn != 0 ||
       F % pl.bn != 0)
     return hipErrorInvalidValue;
   launch<true>(pl, Wg, Wu, Wu, F, F, 2 * F, K, X, M, nullptr, 0, nullptr, act, ldy, st);

@@ -41,3 +41,11 @@ def walks(cases):
     return [s == "1" for s in
             _ask(["walk %d %d 0 %d %d %d %s" % (nkv, B, W, ns, len(ctx), " ".join(map(str, ctx)))
                   for nkv, B, W, ns, ctx in cases])]
+
+
+def gemm_plans(cases):
+    """(tile size, k parts, stages, part boundaries) of every projection (n0, n1, N,
+    K, M, slab floats)."""
+    out = [list(map(int, s.split())) for s in
+           _ask(["gemm " + " ".join(map(str, c)) for c in cases])]
+    return [(o[0], o[1], o[2], o[3:]) for o in out]

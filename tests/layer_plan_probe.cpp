@@ -7,6 +7,9 @@
 //     -> 1 if the workgroups' parts cover every sub-chunk once, in order, at
 //        partial numbers of their own below the plan's bound, where the combine
 //        looks for them; else 0
+//   gemm n0 n1 N K M floats
+//     -> tile size and k parts of a projection, the stages of k and the first of
+//        each part, and at the end their number
 #include <cstdio>
 #include <iostream>
 #include <sstream>
@@ -95,6 +98,15 @@ int main() {
       const AttnPlan f = attn_plan_fit(L, batch, B, C, room);
       printf("%zu %d %d %zu %zu %d %d %zu %zu\n", attn_slots(L, B), d.W, d.ns, d.parts, room, f.W,
              f.ns, f.parts, attn_parts_max(L, batch, B));
+    } else if (what == "gemm") {
+      int n0, n1, N, K, M;
+      size_t floats;
+      in >> n0 >> n1 >> N >> K >> M >> floats;
+      const LayerPlan g = layer_plan(n0, n1, N, K, M, false, floats);
+      const int nk = K / gemm_stage_k(g.bn);
+      printf("%d %d %d", g.bn, g.S, nk);
+      for (int s = 0; s <= g.S; ++s) printf(" %d", split_first(nk, g.S, s));
+      printf("\n");
     } else {
       int nkv, B, Cmax, W, ns, batch;
       in >> nkv >> B >> Cmax >> W >> ns >> batch;

@@ -139,6 +139,19 @@ def test_layer_projections_as_gemm_with_128_tiles():
     layer.close()
 
 
+def test_layer_projections_split_over_unequal_parts_of_k():
+    """96 positions, output (34 heads) and down projection with K = 4352: 68 stages
+    of 64 k in 8 parts of 8 or 9."""
+    from _layer_plan import gemm_plans
+    assert gemm_plans([(512, 0, 512, 4352, 96, 1 << 24)])[0][:3] == (128, 8, 68)
+    ctx = [0, 129, 700, 64, 7, 513]
+    _say(f"case: layer split-K H=512 heads 34/17 ffn=4352 B=16 batch=6 ctx={ctx}")
+    w, weights, inp = _case(512, 34, 17, 4352, 16, 6, ctx, index=846)
+    h32, hb, layer, _ = _run(w, weights, inp)
+    _check(w, weights, inp, h32, hb)
+    layer.close()
+
+
 def test_layer_projections_split_over_k():
     """96 positions at H = 1024, ffn = 2048: the tiled GEMM's 128 x 128 tiles
     are fewer than the CUs, so the q/k/v (12 tiles, K = 1024), output (8

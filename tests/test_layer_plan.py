@@ -1,12 +1,12 @@
 """How a layer forward is cut up, on the CPU: the attention's workgroups with and
-without room for their partials, and the work list that the attention and its
-combine walk."""
+without room for their partials, the work list that the attention and its combine
+walk, and the parts of k of the projections."""
 import random
 import shutil
 
 import pytest
 
-from _layer_plan import plans, walks
+from _layer_plan import gemm_plans, plans, walks
 
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ compiles the rules")
 
@@ -87,3 +87,31 @@ def test_parts_of_the_largest_work_list():
     """Beyond 2^22 sub-chunks the shares divide in 64 bits."""
     assert all(walks([(64, 32, 512, 0, [1 << 20] * 5), (64, 32, 511, 0, [0, 1 << 20, 65] * 3),
                       (2, 1, 32, 16, [1 << 20])]))
+
+
+@pytest.mark.parametrize("K", [4352, 6912, 11008, 12288])
+@pytest.mark.parametrize("M", [80, 128])
+def test_eight_parts_of_k_for_every_width(K, M):
+    """32 tiles of 128 rows on 256 workgroups: eight parts of k, also where K is an
+    odd multiple of 256 and the stages of 64 do not divide by eight."""
+    bn, S, nk, first = gemm_plans([(4096, 0, 4096, K, M, 1 << 24)])[0]
+    assert (bn, S, nk) == (128, 8, K // 64)
+    assert max(b - a for a, b in zip(first, first[1:])) == -(-nk // 8)
+
+
+def test_parts_of_k_cover_it():
+    rng = random.Random(4)
+    cases = [(N, 0, N, 256 * rng.randint(1, 120), rng.randint(65, 700),
+              rng.choice([0, 1 << 20, 1 << 24]))
+             for N in (256 * rng.randint(1, 48) for _ in range(3000))]
+    uneven = 0
+    for c, (bn, S, nk, first) in zip(cases, gemm_plans(cases)):
+        K = c[3]
+        assert bn in (128, 256) and nk * (64 if bn == 128 else 32) == K, c
+        assert first[0] == 0 and first[-1] == nk and len(first) == S + 1, c
+        sizes = {b - a for a, b in zip(first, first[1:])}
+        assert S == 1 or min(sizes) * K >= 512 * nk, c
+        if len(sizes) > 1:                 # a workgroup's tiles lie 8 apart: one part
+            uneven += 1
+            assert 8 % S == 0 and max(sizes) == min(sizes) + 1, c
+    assert uneven > 50
