@@ -468,11 +468,9 @@ __global__ __launch_bounds__(256) void k_qkrope(
   int C = ctx_len[m / B];
   C = C < 0 ? 0 : (C > Cmax ? Cmax : C);
   // the angle in half turns, pos theta^(-2 l / hd) / pi, and its sine and cosine
-  // in double (exp2 and sincospi cost a third of pow, sin and cos); theta^0 is 1
-  // for every theta, an infinite one too (where 0 lt is not a number)
+  // in double (exp2 and sincospi cost a third of pow, sin and cos)
   const double pos = (double)(C + m % B);
-  const double inv = lane == 0 ? 1.0 : exp2(-2.0 * (double)lane / (double)kHd * lt);
-  const double half = pos * (inv * 0.31830988618379067154);
+  const double half = pos * (exp2(-2.0 * (double)lane / (double)kHd * lt) * 0.31830988618379067154);
   double sd, cd;
   sincospi(half, &sd, &cd);
   const float cs = (float)cd, sn = (float)sd;
@@ -1352,12 +1350,15 @@ static xp_status forward(const xp_layer& L, const LayerBufs& b, const AttnPlan& 
   int sq = 1, so = 1, sd = 1;                    // k splits of q/k/v, output, down
   XP_LINEAR("q/k/v", b, L.Wq, L.Wk, L.Wv, nhd, kvd, ldq, H, b.u, M, nullptr, 0, b.qkv, nullptr,
             ldq, false, &sq, st);
+  // log2 of an infinite base as a finite number that turns frequency 0 alone all
+  // the same (2^(-2 lt / 128) is 0; 0 times infinity would be no number)
+  const double lt = std::min(std::log2((double)L.theta), 1e6);
   // about two workgroups per CU, each wave at least one head slot
   const int qy = std::max(1, std::min((nh + 2 * nkv) / 4, 512 / M));
   XP_STEP("qk-norm/rope",
           hipLaunchKernelGGL(k_qkrope, dim3(M, qy), dim3(256), 0, st, sq > 1 ? b.part : b.qkv, sq,
                              (size_t)M * ldq, ldq, B, nh, nkv, ctx_len, C_max, L.g_q, L.g_k,
-                             L.eps, std::log2((double)L.theta), b.qn, b.kb, b.vb, batch, pre));
+                             L.eps, lt, b.qn, b.kb, b.vb, batch, pre));
 #define XP_ATTN(GG, PB)                                                                      \
   hipLaunchKernelGGL((k_attn<GG, PB>), dim3(ap.W),                                            \
                      dim3(attn_waves(GG, PB) * kWave), 0, st,                                 \
