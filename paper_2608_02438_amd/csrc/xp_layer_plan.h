@@ -178,15 +178,18 @@ constexpr int kLayerSplitMax = 8;
 constexpr int kGemmWgs = 256;       // workgroups of the persistent grid (8 XCDs x 32)
 // k of a stage of the pipeline, the least that a part of k differs by
 constexpr int gemm_stage_k(int bn) { return bn == 128 ? 64 : 32; }
-// The first of the nk stages in part s of S (s = S: nk): the parts are equal, or
-// a stage apart where S does not divide nk.
-constexpr int split_first(int nk, int S, int s) { return s * nk / S; }
-// Unequal parts need S to divide 8: a workgroup's tiles lie 8 apart and are then
-// all of one part, so that one stage count serves them.  (K is a multiple of 256,
-// so only S = 8 on 128 x 128 tiles needs unequal parts, at odd multiples.  Equal
-// parts alone leave it S = 4: ffn 11008, 80 and 128 positions, 151 and 168 us a
-// forward, 144 and 161 with unequal ones.)
-constexpr bool split_ok(int nk, int S) { return nk % S == 0 || 8 % S == 0; }
+// The nk stages in S parts, equal or a stage apart: part s is [first(s), first(s +
+// 1)).  Unequal parts need S to divide 8 (ok): a workgroup's tiles lie 8 apart and
+// are then all of one part, so that one stage count serves them.  (K is a multiple
+// of 256, so only S = 8 on 128 x 128 tiles needs unequal parts, at odd multiples.
+// Equal parts alone leave it S = 4: ffn 11008, 80 and 128 positions, 151 and 168 us
+// a forward, 144 and 161 with unequal ones.)
+struct SplitParts {
+  int q, r8;                        // nk / S, and 8 (nk mod S) / S: no division on the device
+  constexpr SplitParts(int nk, int S) : q(nk / S), r8(nk % S * 8 / S) {}
+  constexpr int first(int s) const { return s * q + (s * r8 >> 3); }
+  static constexpr bool ok(int nk, int S) { return nk % S == 0 || 8 % S == 0; }
+};
 // Tile size and parts of k of one projection: among 128 x 128 and 256 x 256
 // tiles (bn dividing every stacked weight's rows) and S = 1 .. kLayerSplitMax
 // (at least 512 k in every part, S M N fp32 slab values within part_floats; GLU:
@@ -207,7 +210,7 @@ inline LayerPlan layer_plan(int n0, int n1, int N, int K, int M, bool glu, size_
     const double rate = bn == 128 ? 3.6e12 : 4.3e12;
     const long tiles = (long)(N / bn) * ((M + bn - 1) / bn);
     for (int S = 1; S <= (glu ? 1 : kLayerSplitMax); ++S) {
-      if (!split_ok(nk, S) || (S > 1 && nk / S < 512 / gk)) continue;
+      if (!SplitParts::ok(nk, S) || (S > 1 && nk / S < 512 / gk)) continue;
       if (S > 1 && (double)S * M * N > (double)part_floats) continue;
       const long items = tiles * S;
       const double rounds = (double)((items + kGemmWgs - 1) / kGemmWgs);

@@ -36,13 +36,14 @@ static_assert(GemmShape<128, 128>::GK == gemm_stage_k(128) &&
 template <int BN, bool GLU>
 struct LayerRows {
   const uint16_t *W0, *W1, *W2;
-  int n0, n1, K, S, nk;
+  int n0, n1, K, S;
+  SplitParts parts;
   const GemmSched* sc;
   const uint16_t *w = nullptr, *wu = nullptr;
   int xk = 0;
   __device__ void prep(int ti) {
-    const int v = sc->tile(ti), rt = v / S, s = v - rt * S;
-    xk = split_first(nk, S, s) * GemmShape<BN, BN>::GK;
+    const int v = sc->tile(ti), rt = GLU ? v : v / S, s = GLU ? 0 : v - rt * S;
+    xk = parts.first(s) * GemmShape<BN, BN>::GK;
     if constexpr (GLU) {
       const size_t f0 = (size_t)rt * (BN / 2);
       w = W0 + f0 * K + xk;
@@ -139,22 +140,23 @@ struct LayerEpi {
 };
 
 // N stacked rows (GLU: 2F, gate and up), S parts of k.  A workgroup's tiles have
-// parts of one length: where the lengths differ S divides 8 (split_ok), and the
-// tiles, 8 apart, are all of one part.
+// parts of one length: where the lengths differ S divides 8, and the tiles, 8
+// apart from number xcd on, are all of one part.
 template <int BN, int BM, bool GLU>
 __global__ __launch_bounds__(kGWaves * kWave) void k_layer_gemm(
     const uint16_t* __restrict__ W0, const uint16_t* __restrict__ W1,
     const uint16_t* __restrict__ W2, int n0, int n1, int N, int K, int S,
-    const uint16_t* __restrict__ X, int M, int nMb, int gpx, const float* __restrict__ R,
-    int ldr, float* __restrict__ Y, size_t slab, uint16_t* __restrict__ Yb, int ldy) {
+    SplitParts parts, const uint16_t* __restrict__ X, int M, int nMb, int gpx,
+    const float* __restrict__ R, int ldr, float* __restrict__ Y, size_t slab,
+    uint16_t* __restrict__ Yb, int ldy) {
   __shared__ u32x4 lds[GemmShape<BN, BM>::SLOTS];                  // [stage][W | X]
   const GemmSched sc(nMb, gpx);
   const int ntl = sc.count(N / BN * S);
   if (ntl == 0) return;                                            // whole workgroup
   constexpr int GK = GemmShape<BN, BM>::GK;
-  const int p0 = sc.mb * BM, nk = K / GK, s0 = sc.tile(0) % S;
-  const int kt = (split_first(nk, S, s0 + 1) - split_first(nk, S, s0)) * GK;
-  LayerRows<BN, GLU> rows{W0, W1, W2, n0, n1, K, S, nk, &sc};
+  const int p0 = sc.mb * BM, s0 = sc.xcd & (S - 1);              // (their part, if they differ)
+  const int kt = (parts.first(s0 + 1) - parts.first(s0)) * GK;
+  LayerRows<BN, GLU> rows{W0, W1, W2, n0, n1, K, S, parts, &sc};
   LayerEpi<BN, BM, GLU> epi{&sc, R, Y, Yb, M, ldr, ldy, p0, S, slab};
   gemm_tiles<BN, BM>(rows, epi, X, K, M, kt, ntl, p0, lds);
 }
@@ -168,12 +170,15 @@ static void launch(LayerPlan pl, const uint16_t* W0, const uint16_t* W1, const u
   const int per = gemm_per_xcd(nMb);              // workgroups per XCD: whole position groups
   const int gpx = per / nMb;
   const size_t slab = (size_t)M * ldy;
+  const SplitParts parts(K / gemm_stage_k(bm), pl.S);
   if (bm == 128)
     hipLaunchKernelGGL((k_layer_gemm<128, 128, GLU>), dim3(8 * per), dim3(kGWaves * kWave), 0, st,
-                       W0, W1, W2, n0, n1, N, K, pl.S, X, M, nMb, gpx, R, ldr, Y, slab, Yb, ldy);
+                       W0, W1, W2, n0, n1, N, K, pl.S, parts, X, M, nMb, gpx, R, ldr, Y, slab, Yb,
+                       ldy);
   else
     hipLaunchKernelGGL((k_layer_gemm<256, 256, GLU>), dim3(8 * per), dim3(kGWaves * kWave), 0, st,
-                       W0, W1, W2, n0, n1, N, K, pl.S, X, M, nMb, gpx, R, ldr, Y, slab, Yb, ldy);
+                       W0, W1, W2, n0, n1, N, K, pl.S, parts, X, M, nMb, gpx, R, ldr, Y, slab, Yb,
+                       ldy);
 }
 
 hipError_t launch_layer_gemm(LayerPlan pl, const uint16_t* W0, const uint16_t* W1,
@@ -181,7 +186,7 @@ hipError_t launch_layer_gemm(LayerPlan pl, const uint16_t* W0, const uint16_t* W
                              int M, const float* R, int ldr, float* Y, uint16_t* Yb, int ldy,
                              hipStream_t st) {
   if ((pl.bn != 128 && pl.bn != 256) || pl.S < 1 || K % gemm_stage_k(pl.bn) != 0 ||
-      !split_ok(K / gemm_stage_k(pl.bn), pl.S) || N % pl.bn != 0 || n0 % pl.bn != 0 ||
+      !SplitParts::ok(K / gemm_stage_k(pl.bn), pl.S) || N % pl.bn != 0 || n0 % pl.bn != 0 ||
       n1 % pl.bn != 0 || (pl.S > 1 && (R || Yb || !Y || ldy != N)))
     return hipErrorInvalidValue;
   launch<false>(pl, W0, W1, W2, n0, n1, N, K, X, M, R, ldr, Y, Yb, ldy, st);

@@ -105,7 +105,7 @@ int main() {
       const LayerPlan g = layer_plan(n0, n1, N, K, M, false, floats);
       const int nk = K / gemm_stage_k(g.bn);
       printf("%d %d %d", g.bn, g.S, nk);
-      for (int s = 0; s <= g.S; ++s) printf(" %d", split_first(nk, g.S, s));
+      for (int s = 0; s <= g.S; ++s) printf(" %d", SplitParts(nk, g.S).first(s));
       printf("\n");
     } else {
       int nkv, B, Cmax, W, ns, batch;
