@@ -907,10 +907,9 @@ __global__ __launch_bounds__(attn_waves(GRP, NPB) * kWave, attn_occ(GRP, NPB)) v
 // parts in order, attn = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s, to bf16
 // (m in the base-2 units of k_attn).  Lane j takes the (m, l) of part s0 + j; the
 // O rows are then read several parts at a time and added in order, all heads'
-// loads in flight together.  HW is the whole group where the waves are many
-// (one head each, three dependent loads for two outputs a lane, took 56 us at
-// batch 64 x 32), one where they are few and the parts many.  A part whose l is
-// 0 (no visible key) contributes nothing.
+// loads in flight together.  HW is the whole group where its waves still fill the
+// chip (the forward's rule), else one.  A part whose l is 0 (no visible key)
+// contributes nothing.
 template <int GRP, int HW>
 __global__ __launch_bounds__(256) void k_attn_comb(const float* __restrict__ opart,
                                                    const float* __restrict__ mlpart, int M, int B,
@@ -973,7 +972,7 @@ __global__ __launch_bounds__(256) void k_attn_comb(const float* __restrict__ opa
       Ll[h] += f[h] * ls;
     }
     const int cnt = ns - s0 < kWave ? ns - s0 : kWave;
-    constexpr int kU = HW >= 8 ? 4 : 8;
+    constexpr int kU = 8;
     auto add = [&](int j0, auto un) {             // parts j0 .. j0 + U - 1
       constexpr int U = un;
       float v0[U][HW], v1[U][HW];
@@ -1377,19 +1376,23 @@ static xp_status forward(const xp_layer& L, const LayerBufs& b, const AttnPlan& 
     else XP_STEP("attention", XP_ATTN(8, 2));
   }
 #undef XP_ATTN
-  // whole groups from 1024 waves on
+  // Whole groups of 2 or 4 from 8192 waves on, else a wave per head.  us, a wave per
+  // head and per group: group 4, 1024 (position, KV head) pairs 5.9 and 7.4, 4096
+  // 11.6 and 11.8 (fewer parts: 13.7 and 15.4), 8192 20.3 and 18.6, 16384 39.4 and
+  // 37.7; group 2, 8192 11.3 and 10.2; group 8, 4096 18.5 and 19.8, 8192 31.7 and
+  // 32.0
 #define XP_COMB1(GG, HH)                                                                     \
   hipLaunchKernelGGL((k_attn_comb<GG, HH>), dim3((M * nkv * (GG / HH) + 3) / 4), dim3(256), 0, \
                      st, b.opart, b.mlpart, M, B, npb, nkv, batch, pre, ap.W, ap.ns, b.attn)
 #define XP_COMB(GG)                                                                          \
   do {                                                                                       \
-    if (M * nkv >= 1024) XP_STEP("attention combine", XP_COMB1(GG, GG));                      \
+    if (M * nkv >= 8192) XP_STEP("attention combine", XP_COMB1(GG, GG));                      \
     else XP_STEP("attention combine", XP_COMB1(GG, 1));                                       \
   } while (0)
   if (grp == 1) XP_STEP("attention combine", XP_COMB1(1, 1));
   else if (grp == 2) XP_COMB(2);
   else if (grp == 4) XP_COMB(4);
-  else XP_COMB(8);
+  else XP_STEP("attention combine", XP_COMB1(8, 1));
 #undef XP_COMB1
 #undef XP_COMB
   XP_LINEAR("output", b, L.Wo, nullptr, nullptr, H, 0, H, nhd, b.attn, M, b.x32, H, b.x1,
