@@ -305,6 +305,10 @@ xp_status xp_layer_create(const xp_layer_weights* w, int32_t max_batch, int32_t 
  * key visible (the drafter's bidirectional block).
  * Calls on one layer share its workspace: issue them in stream order (one
  * stream, or streams synchronized between calls).
+ * The same call gives the same bits.  A sequence's output depends on the others
+ * only through the fp32 summation order: the attention cuts the keys of all
+ * sequences of a call into equal shares, so where a context is split, and the
+ * projections' tiles, follow the call's sizes and every ctx_len.
  * Every pointer 16-byte aligned.
  * Errors: XP_EINVAL (null handle or input, a misaligned pointer, batch, B or
  * C_max outside what the layer was created for), before any launch; XP_EHIP

@@ -1,8 +1,8 @@
 """The attention's shares of the context against the fp64 oracle (needs an
 MI355X): calls whose work list is shorter than the workgroups, one sequence cut
 into many parts, many short sequences in one share, shares that end inside the
-block's own keys, every group size and both block widths, and the static-scratch
-forward where its partials do not fit."""
+block's own keys, every group size and both block widths, a sequence beside others
+of changing length, and the static-scratch forward where its partials do not fit."""
 import numpy as np
 import pytest
 
@@ -55,6 +55,44 @@ def test_attention_shares(nkv, grp, B, ctx, causal):
                                     inp.ctx_len[some], causal=causal)
     # the layer parity tests' bar: one bf16 unit at the output's scale
     assert np.abs(h[some] - ref).max() <= max(2e-2, 2.0 ** -8 * np.abs(ref).max())
+
+
+def test_other_sequences_contexts_move_only_the_summation_order():
+    """The shares are cut from all contexts of a call: with the others' lengths a
+    sequence is split elsewhere.  Both results lie within the parity bar of the
+    oracle; the others' contents change nothing."""
+    import torch
+    from paper_2608_02438_amd.xpress import Layer, device_tensor
+    nkv, nh, B, cmax = 2, 8, 16, 5000
+    w = synth.scaled(synth.configs.QWEN_B1, index=983, H=256, B=B, batch=3, n_heads=nh,
+                     n_kv_heads=nkv, ffn=256, ctx_len=None, ctx_len_range=None)
+    weights = synth.make_layer_weights(w)
+    inp = synth.make_layer_inputs(w, c_max=cmax)
+    dw = {k: device_tensor(weights[k]) for k in LAYER_WEIGHT_NAMES}
+    layer = Layer(dw, w.H, nh, nkv, w.ffn, max_batch=3, max_B=B, max_ctx=cmax)
+    x, kc, vc = (device_tensor(a) for a in (inp.x, inp.k_cache, inp.v_cache))
+    LP = O.layer_ref.LayerParams.from_arrays(weights, nh, nkv, 128)
+    ctx = [4000, 3000, 20]
+    ref = O.layer_ref.layer_forward(LP, inp.x[:1], inp.k_cache[:1], inp.v_cache[:1],
+                                    np.array(ctx[:1], dtype=np.int32))
+    bar = max(2e-2, 2.0 ** -8 * np.abs(ref).max())
+    out = []
+    for others in ([3000, 20], [0, 5000], [4999, 4999]):
+        print(f"shares: contexts {ctx[:1] + others}", flush=True)
+        cl = torch.tensor(ctx[:1] + others, dtype=torch.int32, device="cuda")
+        h, hb = layer.forward(x, kc, vc, cl)
+        out.append(h[0].cpu().numpy())
+        assert np.abs(out[-1] - ref[0]).max() <= bar
+    print(f"  max difference {max(np.abs(o - out[0]).max() for o in out):.3g}, bar {bar:.3g}",
+          flush=True)
+    assert all(np.abs(o - out[0]).max() <= bar for o in out)
+    # the others' inputs, not their lengths: the same bits
+    x2, kc2 = x.clone(), kc.clone()
+    x2[1:] *= -1
+    kc2[1:] *= -1
+    h, _ = layer.forward(x2, kc2, vc, cl)
+    assert np.array_equal(h[0].cpu().numpy().view(np.uint32), out[-1].view(np.uint32))
+    layer.close()
 
 
 # more partials than the static scratch holds beside the buffers: fewer shares, one
