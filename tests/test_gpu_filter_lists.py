@@ -14,9 +14,10 @@ pytestmark = pytest.mark.gpu
 STRESS = dict(W_e=1.0, W_r=0.3, L=0.3, W_in=0.08, W_1=0.08, W_2=0.06)
 
 
-# V = 20011: 1251 tiles, 1256 Read units of one tile, 314 LM-head GEMM units (or
-# 256 of the stream) and 313 target units, so k = 313, 314 and 1256 end the list
-# in one kernel and not in another; 1024 is the list's largest k
+# V = 20011: 1251 tiles, 2048 Read units of at most one tile (797 of them empty),
+# 314 LM-head GEMM units (or 256 of the stream) and 313 target units, so k = 256,
+# 313 and 314 end the list in one kernel and not in another; 1024 is the list's
+# largest k, in the Read's rows too
 @pytest.mark.parametrize("dtype,B,batch", [("bf16", 5, 2), ("bf16", 6, 8), ("f32", 5, 4)])
 @pytest.mark.parametrize("ks", [[1, 2, 255, 256], [257, 313, 314, 315],
                                 [1023, 1024, 1025, 1256], [1257, 20010, 0, 64]])
@@ -31,6 +32,22 @@ def test_top_k_limits(dtype, B, batch, ks):
     run = _check(prob, ref, dev, max_excused=2)
     again = run_device(ref, prob, dev, early_exit=True)
     assert np.array_equal(again.ids, run.ids)
+
+
+# V = 6397: 400 tiles, 800 Read units of which half are empty, 100 LM-head GEMM units
+# (or 256 of the stream) and 100 target units: the Read's list ends at its own number
+# of units, and past the 400 that hold tokens its bound is the empty ones' maximum
+@pytest.mark.parametrize("dtype,B,batch", [("bf16", 5, 2), ("bf16", 6, 8), ("f32", 5, 4)])
+@pytest.mark.parametrize("ks", [[99, 100, 101, 256], [399, 400, 401, 512],
+                                [799, 800, 801, 1024]])
+def test_top_k_at_the_read_units(dtype, B, batch, ks):
+    ks = (ks * batch)[:batch]
+    ps = [0.9, 1.0, 0.7, 1.0, 1.0, 0.95, 0.5, 1.0][:batch]
+    print(f"top-k at the read units {dtype} B={B} batch={batch} k={ks} p={ps}", flush=True)
+    prob = custom_problem(dtype, H=256, V=6397, B=B, batch=batch, K=3, sigmas=STRESS,
+                          temp="sample", seed=160 + ks[0] + batch,
+                          tau=np.linspace(0.6, 1.4, batch), top_k=ks, top_p=ps)
+    _check(prob, make_refiner(prob), upload(prob), max_excused=2)
 
 
 # every logit equal: k tokens tie with all others, the list overflows, and the
