@@ -2,8 +2,7 @@
 (needs an MI355X).
 
 Small shapes span several k-split chunks of every projection, several
-attention chunks (64-key ones for small calls, 128-key ones for large) with
-ragged context lengths (0, chunk boundaries),
+attention shares with ragged context lengths (0, sub-chunk boundaries),
 every built query-group size, blocks of 1, 8, 16 and 32 positions, and the
 projection paths (streaming up to 64 positions, the tiled GEMM with 128 x 128
 tiles, split over k where those are fewer than the CUs, and 256 x 256 ones
@@ -82,7 +81,7 @@ def _check(w, weights, inp, h32, hb_bits, causal=True, seqs=None):
 
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("H,nh,nkv,ffn,B,batch,ctx", [
-    (256, 4, 2, 512, 8, 3, [600, 3, 256]),          # group 2, three KV chunks, ragged
+    (256, 4, 2, 512, 8, 3, [600, 3, 256]),          # group 2, ragged
     (512, 8, 2, 768, 16, 2, [0, 257]),              # group 4 (the Qwen3 ratio), no context
     (256, 8, 1, 256, 32, 1, [300]),                 # group 8, two position blocks
     (256, 2, 2, 256, 1, 2, [1, 511]),               # group 1, blocks of one position
@@ -115,12 +114,12 @@ def test_rope_base_at_its_ends(theta):
     layer.close()
 
 
-def test_layer_large_call_takes_128_key_chunks():
-    """8 sequences x 8 KV heads x up to 33 chunks of 128 keys: at least 512
-    workgroups, so the forward takes the 128-key attention chunks (smaller
-    calls take 64-key ones); ragged contexts from 0 to 4095 keys."""
+def test_layer_large_call_with_several_sub_chunks_a_workgroup():
+    """8 sequences x 8 KV heads of 1 to 65 sub-chunks of 64 keys, 1800 in all on 512
+    workgroups: shares of 3 or 4 that end inside contexts and run over their ends;
+    ragged contexts from 0 to 4095 keys."""
     ctx = [4000, 3000, 2500, 1, 0, 257, 4095, 100]
-    _say(f"case: layer 128-key chunks H=256 heads 8/8 B=16 batch=8 ctx={ctx}")
+    _say(f"case: layer long shares H=256 heads 8/8 B=16 batch=8 ctx={ctx}")
     w, weights, inp = _case(256, 8, 8, 256, 16, 8, ctx, index=811, c_max=4096)
     h32, hb, layer, _ = _run(w, weights, inp)
     _check(w, weights, inp, h32, hb)

@@ -6,7 +6,7 @@ width, query heads and query-group size (every built group: 1, 2, 4, 8),
 FFN width, block length 1..32, batch sizes on both sides of the projections'
 streaming limit (64 positions) so that the streamed, the tiled and the
 split-K projection paths all occur, ragged context lengths from 0 to a few
-hundred keys past the 64- and 128-key chunk boundaries, causal or full block
+hundred keys past several 64-key sub-chunk boundaries, causal or full block
 attention, and a layer created for a larger batch, block and context than
 the call uses.  The fixed cases in test_gpu_layer.py cover each path on
 purpose; these cover combinations of them, to the same bar.
