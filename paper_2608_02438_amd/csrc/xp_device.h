@@ -68,6 +68,25 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m) {
 }
 __device__ __forceinline__ uint64_t umax64(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
+// The largest of a key column's rows first, first + step, ...: sixteen loads in
+// flight, rows past nkeys repeating the last.
+__device__ __forceinline__ uint64_t key_rows_max(const uint64_t* __restrict__ keys, int nkeys,
+                                                 int M, size_t col, int first, int step) {
+  constexpr int kRows = 16;
+  uint64_t best = kKeyMin;
+  for (int r0 = first; r0 < nkeys; r0 += kRows * step) {
+    uint64_t kv[kRows];
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+      const int r = r0 + j * step;
+      kv[j] = keys[(size_t)(r < nkeys ? r : nkeys - 1) * M + col];
+    }
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) best = umax64(best, kv[j]);
+  }
+  return best;
+}
+
 // The base logits s are stored tile-major: the 16 rows of vocabulary tile t
 // for position p are 64 contiguous bytes at float offset 16 (t Ms + p), so a
 // tile's rows for consecutive positions are contiguous.  Ms is the position
@@ -81,8 +100,7 @@ __host__ __device__ __forceinline__ size_t s_index(int p, int row, int Ms) {
 // instructions (v_permlane16_swap, v_permlane32_swap) instead of an LDS round
 // trip.  With x as both operands the instruction returns, in every lane, the
 // values of lanes l and l ^ 16 (l ^ 32), that of the lower half first, so the
-// max or sum of the pair equals x combined with its partner's value bit for
-// bit (both operations commute).
+// max of the pair is that of x and its partner's value.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float fmax_xor16(float x) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -91,14 +109,6 @@ __device__ __forceinline__ float fmax_xor16(float x) {
 __device__ __forceinline__ float fmax_xor32(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float fadd_xor16(float x) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float fadd_xor32(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // ---------------------------------------------------------------------------

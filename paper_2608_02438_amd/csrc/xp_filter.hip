@@ -22,10 +22,12 @@
 // maximum (its leading 22 bits) is a bound that at least k tokens reach, and
 // few more: only the units whose maximum reaches it are read, their tokens at
 // or above it are listed in vocabulary order in LDS, and top-k, top-p, Z and
-// the choice run on that list.  A row costs its 2 K unit maxima and k units of
-// at most 128 tokens instead of seven passes over V = 151936 logits, two of
-// them fp64 exponentials; a list that overflows kCand (many ties) falls back
-// to the general way.  65 rows at k = 50, p = 0.9: 299 -> 23 us per pass, the seed
+// the choice run on that list.  A row costs its unit maxima (2 K at most) and the
+// tokens of about k units instead of seven passes over V = 151936 logits, two of
+// them fp64 exponentials.  A unit has 64 tokens in a target row, at most 128 in the
+// Read's rows and those of the LM-head GEMM, and a 256th of the vocabulary in the
+// seed of the streamed LM heads (608 tokens).  A list that overflows kCand (many
+// ties) falls back to the general way.  65 rows at k = 50, p = 0.9: 299 -> 23 us per pass, the seed
 // 733 -> 45, the target rows 631 -> 17 + 39, the last token 229 -> 16 us.
 //
 // The general way (top-p alone): the row is re-read by every step:

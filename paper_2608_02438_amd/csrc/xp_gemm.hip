@@ -7,7 +7,8 @@
 // positions.  Two shapes: 256 x 256 for more than 128 positions (the matrix
 // cores, not HBM, bound the time at M = 512), and 128 x 128 up to 128
 // positions, where the launch is HBM-bound and the smaller tile gives 4x more
-// tiles to balance over the CUs and a deeper stage ring.
+// tiles to balance over the CUs and stages of 64 k (whole 128-byte lines of W_lm)
+// in the same five-slot ring.
 //
 // Selection units: the vocabulary tiles are split into U = 2 ceil(ntiles /
 // (BN/16)) units (unit_tile_lo partition, at most BN/32 tiles each); a

@@ -47,7 +47,7 @@ namespace xp {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-constexpr int kGK = 32;             // k per LDS stage
+constexpr int kGK = 32;             // k per LDS stage of a 256 x 256 tile
 constexpr int kGWaves = 8;          // 2 (rows) x 4 (positions) waves
 constexpr int kGLoaders = 4;        // waves that issue the stage loads (0 .. 3)
 constexpr int kGPerXcd = 32;        // workgroups per XCD (one per CU)
@@ -108,8 +108,8 @@ __device__ __forceinline__ void gemm_tiles(Rows& rows, Epi& epi, const uint16_t*
   const bool loader = wave < kGLoaders;                           // wave-uniform
   const int li = wave & (kGLoaders - 1);
 
-  // lane l of a load instruction writes the next slot: LDS row slot / 4,
-  // stored chunk l % 4, which holds logical chunk (l % 4) ^ swz(row)
+  // lane l of a load instruction writes the next slot: LDS row slot / CH,
+  // stored chunk l % CH, which holds logical chunk swz(row, l % CH)
   int wrow[WI], wcol[WI], hrow[HI];
 #pragma unroll
   for (int j = 0; j < WI; ++j) {

@@ -525,7 +525,7 @@ __global__ __launch_bounds__(kFWaves32 * kWave) void k_lmhead_f32(
     }
   };
 
-  // product i of this wave: item wave + 8 i = tile P + block
+  // product i of this wave: item wave + 16 i = tile P + block
   int tile[NI], blk[NI];
   bool pact[NI], samp[NI];
   float pit[NI];

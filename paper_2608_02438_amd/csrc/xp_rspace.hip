@@ -321,20 +321,10 @@ __global__ __launch_bounds__(256) void k_fusemix(
     const bool sample = temp != nullptr && temp[b] != 0;
     const int yo = tid < B ? Y[(size_t)b * B + tid] : 0, yp = tid < B ? Yprev[(size_t)b * B + tid] : 0;
     if (!sample) {
-      constexpr int NRG = 256 / BP, kRows = 16;
+      constexpr int NRG = 256 / BP;
       const int pos = tid % BP, rg = tid / BP;
       const size_t col = (size_t)b * B + (pos < B ? pos : B - 1);
-      uint64_t best = 0;
-      for (int r0 = rg; r0 < nkeys; r0 += kRows * NRG) {
-        uint64_t kv[kRows];
-#pragma unroll
-        for (int j = 0; j < kRows; ++j) {
-          const int row = r0 + j * NRG;              // rows past nkeys repeat the last
-          kv[j] = keys[(size_t)(row < nkeys ? row : nkeys - 1) * M + col];
-        }
-#pragma unroll
-        for (int j = 0; j < kRows; ++j) best = umax64(best, kv[j]);
-      }
+      uint64_t best = key_rows_max(keys, nkeys, M, col, rg, NRG);
 #pragma unroll
       for (int o = BP; o < kWave; o <<= 1) best = umax64(best, shfl_xor_u64(best, o));
       if ((tid & (kWave - 1)) < BP) sbest[tid / kWave][pos] = best;

@@ -215,7 +215,7 @@ __global__ __launch_bounds__(kSelWaves * kWave) void k_select(
     int32_t* __restrict__ traj, double* __restrict__ lse, int32_t* __restrict__ iters,
     int32_t* __restrict__ ctrl, uint32_t* __restrict__ err, int early_exit,
     int32_t* __restrict__ out_ids, int32_t* __restrict__ out_iters, int K) {
-  constexpr int NT = kSelWaves * kWave, kRowsPerRound = 16;
+  constexpr int NT = kSelWaves * kWave;
   const int b = blockIdx.x, t = threadIdx.x;
   __shared__ int changed;
   __shared__ uint64_t sbest[kSelWaves][32];
@@ -239,17 +239,7 @@ __global__ __launch_bounds__(kSelWaves * kWave) void k_select(
     const int PP = B <= 16 ? 16 : 32, NRG = NT / PP;
     const int pos = t % PP, rg = t / PP;
     const size_t col = (size_t)b * B + (pos < B ? pos : B - 1);
-    uint64_t best = 0;
-    for (int r0 = rg; r0 < nkeys; r0 += kRowsPerRound * NRG) {
-      uint64_t kv[kRowsPerRound];
-#pragma unroll
-      for (int j = 0; j < kRowsPerRound; ++j) {
-        const int r = r0 + j * NRG;               // rows past nkeys repeat the last
-        kv[j] = keys[(size_t)(r < nkeys ? r : nkeys - 1) * M + col];
-      }
-#pragma unroll
-      for (int j = 0; j < kRowsPerRound; ++j) best = umax64(best, kv[j]);
-    }
+    uint64_t best = key_rows_max(keys, nkeys, M, col, rg, NRG);
     for (int o = PP; o < kWave; o <<= 1) best = umax64(best, shfl_xor_u64(best, o));
     if ((t & (kWave - 1)) < PP) sbest[t / kWave][pos] = best;
   }
