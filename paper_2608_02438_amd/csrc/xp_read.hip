@@ -5,6 +5,8 @@
 //
 // W_r is streamed once per pass and 16-position block, tile by tile (16
 // vocabulary rows), straight into MFMA operand registers.
+#include <type_traits>
+
 #include "xp_internal.h"
 #include "xp_tiles.h"
 
@@ -222,14 +224,26 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read(
 }
 
 // ---------------------------------------------------------------------------
-// A7 in fp32: one wave per unit, PB 16-position blocks per workgroup (their z in
-// LDS), the next W_r tile in flight while one multiplies.  A block at a time
-// (the form before) read W_r once per 16 positions: 35.6 us a pass at 33
-// positions of V = 33001, bound by those reads and by one chain of dependent
-// matrix operations per wave; PB interleaved chains share every tile.  Each
-// chain is ReadTile::chain's, so the logits are those of the rescans.
+// A7 in fp32: a wave takes the tiles of GS units, PB 16-position blocks per
+// workgroup (their z in LDS).  A block at a time (the form before) read W_r once
+// per 16 positions: 35.6 us a pass at 33 positions of V = 33001, bound by those
+// reads and by one chain of dependent matrix operations per wave; PB interleaved
+// chains share every tile.  Each chain is ReadTile::chain's, so the logits are those
+// of the rescans.
+//
+// ONE: a wave's units hold one tile together at most (GS ntiles <= U).  Then no
+// second tile's registers are kept and two workgroups fit a CU, one's loads under
+// the other's matrix operations.  GS = 2 (vocabularies up to 16384 rows, whose units
+// are at least half empty) keeps all eight waves of a workgroup at work where there
+// are more workgroups than CUs.
+//
+// us a launch, event-timed, one block a workgroup column at a time / the form with
+// one workgroup per CU, the flags behind the tile and no GS / now: V = 4000, 16 / 80 /
+// 512 positions 14 / 12 / 9, 14 / 16 / 11, 43 / 39 / 19; V = 12000, 80 positions 24 /
+// 32 / 16; V = 33001, 48 positions 36 / 25 / 20; V = 151936, 16 / 64 positions 30 /
+// 34 / 33, 102 / 70 / 67.
 // ---------------------------------------------------------------------------
-template <int PB>
+template <int PB, int GS, bool ONE>
 __global__ __launch_bounds__(kReadWaves * kWave) void k_read_f32(
     const float* __restrict__ W, const float* __restrict__ Z, const float* __restrict__ S, int Ms,
     int V, int M, int ntiles, int U, uint64_t* __restrict__ keys, Stat* __restrict__ stats,
@@ -239,14 +253,14 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read_f32(
   using RT = ReadTile<float>;
   constexpr int NU = RT::NU;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int u = blockIdx.x * kReadWaves + wave, p0 = blockIdx.y * (kTile * PB);
-  const int tlo = unit_tile_lo(u, ntiles, U), thi = unit_tile_lo(u + 1, ntiles, U);
+  // the wave's units u0 .. u0 + GS - 1 (none past U) and their tiles
+  const int u0 = (blockIdx.x * kReadWaves + wave) * GS, p0 = blockIdx.y * (kTile * PB);
+  const int ub = u0 < U ? u0 : U, ue = u0 + GS < U ? u0 + GS : U;
+  const int tlo = unit_tile_lo(ub, ntiles, U), thi = unit_tile_lo(ue, ntiles, U);
   const int tl = thi > tlo ? tlo : (tlo < ntiles ? tlo : ntiles - 1);   // an empty unit loads a tile it drops
   __shared__ u32x4 zl[PB][NU][64];
   __shared__ uint64_t kred[kReadWaves][PB * kTile];
 
-  u32x4 a[NU], an[NU];
-  floatx4 c[PB], cn[PB];
   int pc[PB];
   bool act[PB], sample[PB];
 #pragma unroll
@@ -261,80 +275,141 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read_f32(
       s4[pb] = *reinterpret_cast<const floatx4*>(S + s_index(pc[pb], t * kTile + 4 * (lane >> 4), Ms));
     RT::load_w(W, V, t, lane, w);
   };
-  // z fragments of the blocks, 16-byte chunks in turn over the threads
-  constexpr int kZPer = PB * NU * 64 / (kReadWaves * kWave);
-  u32x4 zv[kZPer];
-#pragma unroll
-  for (int j = 0; j < kZPer; ++j) {
-    const int ch = threadIdx.x + kReadWaves * kWave * j;
-    const int pb = ch / (NU * 64), zi = (ch / 64) % NU, zlane = ch % 64;
-    const int zp = p0 + kTile * pb + (zlane & 15);
-    zv[j] = ld16(Z + (size_t)(zp < M ? zp : M - 1) * 256 + (zlane >> 4) * RT::EPB + zi * RT::KU);
-  }
-  asm volatile("" ::: "memory");
-  load(tl, a, c);
-  asm volatile("" ::: "memory");
   uint64_t best[PB];
   Stat st[PB];
   float pit[PB];
+  // LONG: a unit of two tiles or more.  One block keeps its z in registers and takes
+  // a tile at a time (V = 60000 16.6 us; two in flight 19.2 to 23.6: its waves wait
+  // for memory, not for each other).  More blocks have two tiles in flight, in loops
+  // whose loads are neither conditional (a wait past a join of both cases waits for
+  // the later tile too) nor in vain; with four blocks that form spills, and the
+  // short loop is the faster one (66.6 against 71.2 us at V = 151936).
+  auto run = [&](auto longer) __attribute__((always_inline)) {
+    constexpr bool LONG = decltype(longer)::value, kZReg = LONG && PB == 1;
+    u32x4 a[NU], an[LONG ? NU : 1];
+    floatx4 c[PB], cn[LONG ? PB : 1];
+    // z fragments of the blocks, 16-byte chunks in turn over the threads; they and the
+    // flags go out first, so that only they are waited for before the barrier
+    constexpr int kZPer = PB * NU * 64 / (kReadWaves * kWave);
+    u32x4 zv[kZPer];
 #pragma unroll
-  for (int pb = 0; pb < PB; ++pb) {
-    sample[pb] = act[pb] && load_flag(temp, pc[pb] / B, S) != 0;
-    pit[pb] = invT[pc[pb] / B];
-    best[pb] = kKeyMin;
-    st[pb] = stat_empty();
-  }
-#pragma unroll
-  for (int j = 0; j < kZPer; ++j) {
-    const int ch = threadIdx.x + kReadWaves * kWave * j;
-    const int zp = p0 + kTile * (ch / (NU * 64)) + (ch & 15);
-    zl[ch / (NU * 64)][(ch / 64) % NU][ch % 64] = zp < M ? zv[j] : u32x4{0u, 0u, 0u, 0u};
-  }
-  lds_barrier();
-  auto tile = [&](const u32x4 (&w)[NU], const floatx4 (&s4)[PB], int t) {
-    floatx4 acc[PB];
-#pragma unroll
-    for (int pb = 0; pb < PB; ++pb) acc[pb] = act[pb] ? s4[pb] : floatx4{0.f, 0.f, 0.f, 0.f};
-    // z one load unit ahead (all of it at once would not fit the registers)
-    u32x4 z[2][PB];
-#pragma unroll
-    for (int pb = 0; pb < PB; ++pb) z[0][pb] = zl[pb][0][lane];
-#pragma unroll
-    for (int i = 0; i < NU; ++i) {
-      if (i + 1 < NU) {
-#pragma unroll
-        for (int pb = 0; pb < PB; ++pb) z[(i + 1) & 1][pb] = zl[pb][i + 1][lane];
-      }
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int pb = 0; pb < PB; ++pb) acc[pb] = Mfma<float>::mma(w[i], z[i & 1][pb], acc[pb]);
+    for (int j = 0; j < kZPer; ++j) {
+      const int ch = threadIdx.x + kReadWaves * kWave * j;
+      const int pb = ch / (NU * 64), zi = (ch / 64) % NU, zlane = ch % 64;
+      const int zp = p0 + kTile * pb + (zlane & 15);
+      zv[j] = ld16(Z + (size_t)(zp < M ? zp : M - 1) * 256 + (zlane >> 4) * RT::EPB + zi * RT::KU);
     }
-    const int row0 = t * kTile + 4 * (lane >> 4);
+    int tv[PB];
 #pragma unroll
     for (int pb = 0; pb < PB; ++pb) {
-      const int p = p0 + kTile * pb + (lane & 15);
+      tv[pb] = load_flag(temp, pc[pb] / B, S);
+      pit[pb] = invT[pc[pb] / B];
+    }
+    asm volatile("" ::: "memory");
+    load(tl, a, c);
+    if constexpr (LONG && PB > 1) load(tlo + 1, an, cn);
+    asm volatile("" ::: "memory");
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const bool v = act[pb] && row0 + i < V;
-        const uint64_t key = umax64(best[pb], argmax_key(acc[pb][i], (uint32_t)(row0 + i)));
-        best[pb] = v && !sample[pb] ? key : best[pb];
-        if (sample[pb] && v) st[pb] = stat_merge(st[pb], Stat{acc[pb][i] * pit[pb], 1.f});
+    for (int pb = 0; pb < PB; ++pb) {
+      sample[pb] = act[pb] && tv[pb] != 0;
+      best[pb] = kKeyMin;
+      st[pb] = stat_empty();
+    }
+#pragma unroll
+    for (int j = 0; j < kZPer; ++j) {
+      const int ch = threadIdx.x + kReadWaves * kWave * j;
+      const int zp = p0 + kTile * (ch / (NU * 64)) + (ch & 15);
+      zl[ch / (NU * 64)][(ch / 64) % NU][ch % 64] = zp < M ? zv[j] : u32x4{0u, 0u, 0u, 0u};
+    }
+    lds_barrier();
+    u32x4 zr[kZReg ? NU : 1];                     // one block's z stays in registers
+    if constexpr (kZReg) {
+#pragma unroll
+      for (int i = 0; i < NU; ++i) zr[i] = zl[0][i][lane];
+    }
+    auto tile = [&](const u32x4 (&w)[NU], const floatx4 (&s4)[PB], int t) {
+      floatx4 acc[PB];
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) acc[pb] = act[pb] ? s4[pb] : floatx4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (kZReg) {
+#pragma unroll
+        for (int i = 0; i < NU; ++i) acc[0] = Mfma<float>::mma(w[i], zr[i], acc[0]);
+      } else {
+        // z one load unit ahead (all of it at once would not fit the registers)
+        u32x4 z[2][PB];
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) z[0][pb] = zl[pb][0][lane];
+#pragma unroll
+        for (int i = 0; i < NU; ++i) {
+          if (i + 1 < NU) {
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) z[(i + 1) & 1][pb] = zl[pb][i + 1][lane];
+          }
+          asm volatile("" ::: "memory");
+#pragma unroll
+          for (int pb = 0; pb < PB; ++pb) acc[pb] = Mfma<float>::mma(w[i], z[i & 1][pb], acc[pb]);
+        }
       }
-      if (act[pb] && rows.out) put_rows(rows.out, (size_t)p * V + row0, acc[pb], row0, V, rows.vec);
-      if (act[pb] && rows.lf && rows.filt[pc[pb] / B])
-        put_rows(rows.lf, (size_t)p * V + row0, acc[pb], row0, V, rows.vec);
+      const int row0 = t * kTile + 4 * (lane >> 4);
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) {
+        const int p = p0 + kTile * pb + (lane & 15);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bool v = act[pb] && row0 + i < V;
+          const uint64_t key = umax64(best[pb], argmax_key(acc[pb][i], (uint32_t)(row0 + i)));
+          best[pb] = v && !sample[pb] ? key : best[pb];
+          if (sample[pb] && v) st[pb] = stat_merge(st[pb], Stat{acc[pb][i] * pit[pb], 1.f});
+        }
+        if (act[pb] && rows.out) put_rows(rows.out, (size_t)p * V + row0, acc[pb], row0, V, rows.vec);
+        if (act[pb] && rows.lf && rows.filt[pc[pb] / B])
+          put_rows(rows.lf, (size_t)p * V + row0, acc[pb], row0, V, rows.vec);
+      }
+    };
+    if constexpr (LONG && PB == 1) {
+#pragma unroll 1
+      for (int t = tlo; t < thi; ++t) {
+        if (t > tlo) load(t, a, c);
+        tile(a, c, t);
+      }
+    } else if constexpr (LONG && PB == 4) {
+#pragma unroll 1
+      for (int t = tlo; t < thi; t += 2) {
+        tile(a, c, t);
+        if (t + 1 >= thi) break;
+        if (t + 2 < thi) load(t + 2, a, c);
+        tile(an, cn, t + 1);
+        if (t + 3 < thi) load(t + 3, an, cn);
+      }
+    } else if constexpr (LONG) {
+      int t = tlo;
+#pragma unroll 1
+      for (; t + 3 < thi; t += 2) {
+        tile(a, c, t);
+        load(t + 2, a, c);
+        tile(an, cn, t + 1);
+        load(t + 3, an, cn);
+      }
+      if (t + 2 < thi) {
+        tile(a, c, t);
+        load(t + 2, a, c);
+        tile(an, cn, t + 1);
+        tile(a, c, t + 2);
+      } else {
+        tile(a, c, t);
+        tile(an, cn, t + 1);
+      }
+    } else if (tlo < thi) {
+      tile(a, c, tlo);
     }
   };
-  if (thi - tlo == 1) {
-    tile(a, c, tlo);
+  if constexpr (ONE) {
+    run(std::false_type{});
   } else {
-    for (int t = tlo; t < thi; t += 2) {
-      load(t + 1 < thi ? t + 1 : thi - 1, an, cn);
-      tile(a, c, t);
-      if (t + 1 >= thi) break;
-      load(t + 2 < thi ? t + 2 : thi - 1, a, c);
-      tile(an, cn, t + 1);
-    }
+    if (thi - tlo > 1)                            // wave-uniform
+      run(std::true_type{});
+    else
+      run(std::false_type{});
   }
 #pragma unroll
   for (int pb = 0; pb < PB; ++pb) {
@@ -344,15 +419,29 @@ __global__ __launch_bounds__(kReadWaves * kWave) void k_read_f32(
       const Stat o{__shfl_xor(st[pb].m, m, kWave), __shfl_xor(st[pb].s, m, kWave)};
       st[pb] = stat_merge(st[pb], o);
     }
-    if (lane < 16 && sample[pb]) stats[(size_t)(p0 + kTile * pb + lane) * U + u] = st[pb];
+    if (lane < 16 && sample[pb]) {
+#pragma unroll
+      for (int q = 0; q < GS; ++q) {                // (ONE: the tile is in one of the units)
+        const int u = u0 + q;
+        if (u < U)
+          stats[(size_t)(p0 + kTile * pb + lane) * U + u] =
+              GS == 1 || unit_tile_lo(u + 1, ntiles, U) > unit_tile_lo(u, ntiles, U)
+                  ? st[pb] : stat_empty();
+      }
+    }
     if (lane < 16) kred[wave][kTile * pb + lane] = best[pb];
   }
   __syncthreads();
   if (threadIdx.x < PB * kTile) {
-    uint64_t b = kKeyMin;
-    for (int w = 0; w < kReadWaves; ++w) b = umax64(b, kred[w][threadIdx.x]);
     const int pp = p0 + threadIdx.x;
-    if (pp < M) keys[(size_t)blockIdx.x * M + pp] = b;
+#pragma unroll
+    for (int q = 0; q < GS; ++q) {                  // the key rows of GS read workgroups
+      const int row = blockIdx.x * GS + q;
+      uint64_t b = kKeyMin;
+      for (int w = 0; w < kReadWaves / GS; ++w)
+        b = umax64(b, kred[q * (kReadWaves / GS) + w][threadIdx.x]);
+      if (pp < M && row * kReadWaves < U) keys[(size_t)row * M + pp] = b;
+    }
   }
 }
 
@@ -734,26 +823,56 @@ hipError_t launch_read(xp_handle* h, int batch, uint32_t flags, const uint8_t* t
       go(k_read<false>);
     return hipGetLastError();
   }
-  // fp32: up to 4 position blocks per workgroup, as many as make one workgroup
-  // per CU (its registers allow no second one): V = 33001 at 33 positions takes
-  // three (36 -> 26 us a pass), a vocabulary of few workgroups one each
-  const int nb = (M + kTile - 1) / kTile;
-  int PB = (h->read_wgs * nb + h->cus - 1) / h->cus;
-  PB = PB < 4 ? PB : 4;
-  PB = PB < nb ? PB : nb;
-  const int ny = (nb + PB - 1) / PB;
-  PB = (nb + ny - 1) / ny;
-  grid = dim3(h->read_wgs, (nb + PB - 1) / PB);
-#define XP_RF(PP)                                                                             \
-  hipLaunchKernelGGL((k_read_f32<PP>), grid, block, 0, st, (const float*)h->W_r,               \
+  // fp32: a wave takes two units where each is at least half empty and one apiece
+  // would make more workgroups than CUs (V = 12000, 80 positions: 32 -> 16 us)
+  const int nb = (M + kTile - 1) / kTile, cus = h->cus;
+  const int GS = 2 * h->ntiles <= h->read_units && h->read_wgs * nb > cus ? 2 : 1;
+  const int gx = (h->read_wgs + GS - 1) / GS;
+  const bool one = GS * h->ntiles <= h->read_units;
+  auto ny = [&](int pb) { return (nb + pb - 1) / pb; };
+  // Position blocks per workgroup.  Units of one tile: the least of the launch's
+  // times, which go with a + b ceil(workgroups / CUs) (us, event-timed, V = 1000 to
+  // 32768 at 16 to 512 positions: what it picks is the fastest of the three there,
+  // within 5%).  Longer units (one workgroup per CU): as many as four.
+  int PB = 1;
+  if (one) {
+    constexpr float a[3] = {6.7f, 7.5f, 8.8f}, b[3] = {4.9f, 6.8f, 8.7f};
+    float least = 0.f;
+    for (int pb = 1; pb <= 3; ++pb) {
+      const float t = a[pb - 1] + b[pb - 1] * (float)((gx * ny(pb) + cus - 1) / cus);
+      if (pb == 1 || t < least) {
+        PB = pb;
+        least = t;
+      }
+    }
+  } else {
+    PB = nb < 4 ? nb : 4;
+  }
+  PB = (nb + ny(PB) - 1) / ny(PB);                // spread evenly
+  grid = dim3(gx, ny(PB));
+#define XP_RF(PP, GG, OO)                                                                     \
+  hipLaunchKernelGGL((k_read_f32<PP, GG, OO>), grid, block, 0, st, (const float*)h->W_r,       \
                      (const float*)h->ws.z, h->ws.s, M, h->V, M, h->ntiles, h->read_units,     \
                      h->ws.keys, h->ws.stats, temp, h->B, rows, h->ws.ctrl, skip, h->ws.invT)
-  switch (PB) {
-    case 1: XP_RF(1); break;
-    case 2: XP_RF(2); break;
-    case 3: XP_RF(3); break;
-    default: XP_RF(4);
+#define XP_RF_ONE(GG)                                                                         \
+  switch (PB) {                                                                               \
+    case 1: XP_RF(1, GG, true); break;                                                        \
+    case 2: XP_RF(2, GG, true); break;                                                        \
+    default: XP_RF(3, GG, true);                                                              \
   }
+  if (one && GS == 1) {
+    XP_RF_ONE(1)
+  } else if (one) {
+    XP_RF_ONE(2)
+  } else {
+    switch (PB) {
+      case 1: XP_RF(1, 1, false); break;
+      case 2: XP_RF(2, 1, false); break;
+      case 3: XP_RF(3, 1, false); break;
+      default: XP_RF(4, 1, false);
+    }
+  }
+#undef XP_RF_ONE
 #undef XP_RF
   return hipGetLastError();
 }

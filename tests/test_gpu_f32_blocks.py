@@ -19,7 +19,12 @@ STRESS = dict(W_e=1.0, W_r=0.3, L=0.3, W_in=0.08, W_1=0.08, W_2=0.06)
 
 @pytest.mark.parametrize("H,V,B,batch", [
     (256, 6113, 11, 2), (256, 6145, 11, 3), (512, 12289, 16, 4), (512, 40001, 13, 5),
-    (256, 70000, 16, 2), (4096, 6200, 9, 2), (256, 6400, 16, 9), (256, 300, 16, 3)])
+    (256, 70000, 16, 2), (4096, 6200, 9, 2), (256, 6400, 16, 9), (256, 300, 16, 3),
+    # the Read's forms: one tile for a wave's one or two units (an odd number of
+    # read workgroups, the last vocabularies of both forms and one row more), one to
+    # three blocks of it a workgroup, and longer units
+    (256, 4000, 16, 5), (256, 4000, 16, 32), (256, 16384, 16, 3), (256, 16384, 16, 12),
+    (256, 16385, 16, 3), (256, 32768, 16, 2), (256, 32769, 11, 3), (256, 50000, 16, 5)])
 def test_blocks_equal_single_sequences(H, V, B, batch):
     import torch
     print(f"fp32 blocks: H={H} V={V} B={B} batch={batch}", flush=True)
