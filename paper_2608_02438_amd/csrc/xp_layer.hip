@@ -1376,17 +1376,18 @@ static xp_status forward(const xp_layer& L, const LayerBufs& b, const AttnPlan& 
     else XP_STEP("attention", XP_ATTN(8, 2));
   }
 #undef XP_ATTN
-  // Whole groups of 2 or 4 from 8192 waves on, else a wave per head.  us, a wave per
-  // head and per group: group 4, 1024 (position, KV head) pairs 5.9 and 7.4, 4096
-  // 11.6 and 11.8 (fewer parts: 13.7 and 15.4), 8192 20.3 and 18.6, 16384 39.4 and
-  // 37.7; group 2, 8192 11.3 and 10.2; group 8, 4096 18.5 and 19.8, 8192 31.7 and
-  // 32.0
+  // Whole groups of 2 from 4096 waves on and of 4 from 8192, else a wave per head.
+  // us, a wave per head and per group: group 2, 1024 (position, KV head) pairs 4.7
+  // and 5.1, 2048 5.3 and 5.5, 4096 6.4 and 5.5 (more parts: 7.1 and 5.8), 8192 11.3
+  // and 10.2; group 4, 1024 5.9 and 7.4, 4096 11.6 and 11.8 (fewer parts: 13.7 and
+  // 15.4), 8192 20.3 and 18.6, 16384 39.4 and 37.7; group 8, 4096 18.5 and 19.8,
+  // 8192 31.7 and 32.0
 #define XP_COMB1(GG, HH)                                                                     \
   hipLaunchKernelGGL((k_attn_comb<GG, HH>), dim3((M * nkv * (GG / HH) + 3) / 4), dim3(256), 0, \
                      st, b.opart, b.mlpart, M, B, npb, nkv, batch, pre, ap.W, ap.ns, b.attn)
 #define XP_COMB(GG)                                                                          \
   do {                                                                                       \
-    if (M * nkv >= 8192) XP_STEP("attention combine", XP_COMB1(GG, GG));                      \
+    if (M * nkv >= 2048 * GG) XP_STEP("attention combine", XP_COMB1(GG, GG));                      \
     else XP_STEP("attention combine", XP_COMB1(GG, 1));                                       \
   } while (0)
   if (grp == 1) XP_STEP("attention combine", XP_COMB1(1, 1));
